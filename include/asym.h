@@ -665,7 +665,9 @@ int asym_gemm_bf16_trace(const asym_topology* topo, int M, int N, int K,
  * launching it or touching the matrices: the same checks and errors, the
  * output tile (tile_m x tile_n; the width is taken from 256, 224 and 192 to
  * minimise the rounds of tiles the persistent workers run, Section 7.1's wave
- * quantization), the tile grid, the workgroups launched and the workers that
+ * quantization; 128 x 128 or 128 x 96 where 256 x 256 tiles would leave three
+ * quarters of the workers idle; where the tiles still do not fill the workers,
+ * neighbouring workgroups of one XCD share a tile's parts), the tile grid, the workgroups launched and the workers that
  * take tiles, per XCD and in all.  claims = 1 when the aware mapping hands
  * tiles out through per-XCD counters (CU sets with unequal XCD counts),
  * 0 when every worker walks a fixed list.  vector_path = 1 for 16-byte loads

@@ -231,9 +231,36 @@ struct GemmPlan {
   bool vec = false, dynamic = false, whole = true;
   bool vec_ab = false;  // A and B alone meet the vector-path alignment
   int bn = 0, bm = 256, tiles_m = 0, tiles_n = 0, grid = 0;
+  int pm = 0, pn = 0;  // > 0: tiles computed in parts of pm x pn
   int small_mb = 0;  // > 0: the small-M kernel with this many 16-row blocks
   bool b_transposed = false;  // B stored [K][N]: transposed into a library buffer first
 };
+
+// Products whose tiles do not fill the workers compute each tile in parts, one
+// workgroup each (the deep-ring kernel): the smallest part with which one round
+// of workgroups still covers the product, since a part's time per k-stage grows
+// with its size (64 x 64: 0.21 us, 128 x 64: 0.30, 128 x 96: 0.41, 128 x 128:
+// 0.46, 128 x 192: 0.60, on a full chip) and a second round costs a whole part.
+// Measured (K = 4096, us): 512 x 6144 in 128 x 96 parts 29.4, 128 x 128 31.7,
+// 64 x 64 (three rounds) 44.0; 1024 x 4096 in 128 x 128 33.3, 128 x 64 (two
+// rounds) 43.5.  256-row tiles that fill at most half the workers are cut in
+// two 128 x 192 halves: 1024 x 6144 44.1 against 61.2 in whole 256 x 192 tiles
+// and 58.0 in two rounds of 128 x 128.  Where whole tiles cover more than half
+// the workers the 256-row rings stay (1.4 us per stage for 3 to 4 times the
+// outputs: 2048 x 6144 74.6 whole, 99.8 in 128 x 128).  Each output is the same
+// MFMA chain in every part, so the bits do not change.
+static void choose_parts(int M, int N, GemmPlan* P) {
+  auto tiles = [&](int64_t h, int64_t w) { return ((M + h - 1) / h) * ((N + w - 1) / w); };
+  if (P->bm == 128) {
+    const int64_t t = tiles(128, 128);
+    P->pm = 4 * t <= P->total ? 64 : 128;
+    P->pn = 2 * t <= P->total ? 64 : 128;
+    if (P->pn == 128 && tiles(128, 96) <= P->total) P->bn = P->pn = 96;
+  } else if (2 * tiles(256, 192) <= P->total) {
+    P->bn = P->pn = 192;
+    P->pm = 128;
+  }
+}
 
 // Row pitch (elements) of the transposed copy of a [K][N] operand.
 static int kn_pitch(int K) { return (K + 7) / 8 * 8; }
@@ -443,6 +470,7 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
     P->bm = 128;
     P->bn = 128;
   }
+  if (vec && small_tiles) choose_parts(M, N, P);
   P->tiles_m = (M + P->bm - 1) / P->bm;
   P->tiles_n = (N + P->bn - 1) / P->bn;
   P->grid = mapping == ASYM_MAP_AWARE ? t->n_xccs * smax : total;
@@ -573,6 +601,8 @@ static int gemm_bf16_locked(const asym_topology* topo_in, int M, int N, int K, c
   g.vec = P.vec;
   g.bn = P.bn;
   g.bm = P.bm;
+  g.pm = P.pm;
+  g.pn = P.pn;
   return launch_gemm(g, stream);
 }
 
@@ -655,6 +685,8 @@ int gemm_bf16_scratch(const asym_topology* topo_in, int M, int N, int K, const v
   g.vec = P.vec;
   g.bn = P.bn;
   g.bm = P.bm;
+  g.pm = P.pm;
+  g.pn = P.pn;
   return launch_gemm(g, stream);
 }
 
@@ -691,6 +723,8 @@ int gemm_bf16_trace(const asym_topology* topo_in, int M, int N, int K, const voi
   g.vec = P.vec;
   g.bn = P.bn;
   g.bm = P.bm;
+  g.pm = P.pm;
+  g.pn = P.pn;
   g.d_trace = records;
   *n_records = P.grid;
   return launch_gemm(g, stream);

@@ -41,8 +41,11 @@
 // prefetch.  Tiles 224 and 192 wide (7 and 6 B fragments per wave) exist for
 // shapes whose tile count fits the workers better at those widths.
 //
-// Generic path (any alignment or K): 256x256x64 tiles, register-staged
-// element loads into two padded LDS stages.
+// Part path (the same operands, too few tiles for the chip): tiles cut into
+// parts of 64x64 to 128x192, one workgroup each, through a deeper ring.
+//
+// Generic path (any alignment or K): 256x256 or 128x128 tiles, k-stages of 64,
+// register-staged element loads into two padded LDS stages.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -75,6 +78,8 @@ struct Params {
   int dynamic;       // aware mapping with claims instead of the static assignment
   const int4* desc;  // grouped GEMM: per tile {first row, rows, group's first B row, first column}
   asym_wg_record* trace;  // traced launches: one record per workgroup (null otherwise)
+  int tile_h, tile_w;      // part path: the schedule's tile
+  int parts_n, parts;      // part path: parts across a tile, and in all
 };
 
 // Where a tile lies.  Plain GEMM: tile = row-major index in the tile grid.
@@ -377,7 +382,16 @@ __device__ __forceinline__ void issue_next(NextTile& n) {
     n.v = n.order[n.i_next < n.end ? n.i_next : 0];
 }
 
+template <bool PARTS = false>
 __device__ __forceinline__ int steal_aware(const Params& p, int xcc, int q_lane);
+
+// The j-th part of a region that starts at `base` of the tile order, as
+// tile x parts + part: a tile's parts follow each other, so they go to
+// workgroups of one XCD, which share the tile's rows of A and B in its L2.
+__device__ __forceinline__ int part_item(const Params& p, int base, int j) {
+  const int q = j / p.parts;
+  return __builtin_amdgcn_readfirstlane(p.order[base + q]) * p.parts + (j - q * p.parts);
+}
 
 // Wave 0 (all lanes): the next tile, or -1.  Dynamic: the index claimed by
 // lane 0 is looked up in the XCD's list; once the own region is exhausted,
@@ -726,12 +740,203 @@ __device__ __forceinline__ void compute_tile_ring(const Params& pin, int tile, u
   }
 }
 
+// ---- part path: direct-to-LDS, deep ring, small output parts ------------------------
+// A product with too few 256-row tiles to fill the chip computes each tile of
+// its schedule in parts of (32 FM) x (32 FN) outputs, one workgroup each.
+// What bounds it: the loads into LDS.  A 128 x 128 part takes 32 KiB of them per
+// 64-wide k-stage; alone, with the MFMAs and the LDS reads left out, they take
+// 0.34 us a stage with all CUs busy (97 GB/s per CU), the MFMAs alone 0.30, the
+// LDS reads alone 0.13, all together 0.43.  A wider part needs fewer bytes per
+// output, so parts are as large as one round of workgroups allows.  The loads
+// of a stage take about a microsecond to arrive: the ring holds NS stages (4 of
+// 32 to 40 KiB, 6 of the smaller ones; more measured the same or slower, as the
+// first stage then waits behind more loads), where the register-staged
+// tiles that served these products before had one stage in flight and waited a
+// memory round trip per stage (512 x 6144 x 4096: 55.1 us, now 28.9; 1024 x
+// 4096 x 4096: 59.3, now 33.3; 512^3 kernel time 10.8, now 5.7).  4 waves in a 2 x 2
+// grid, each FM x FN blocks of 16 x 16; loads, LDS image and swizzle as in the
+// rings above (8 lanes per 128-byte line, chunk XOR (row >> 1) & 7).
+//
+// Both 32-wide steps of a stage are in registers before its MFMAs start: the
+// reads of stage t + 1 are issued between the MFMAs of stage t, so a read has a
+// whole stage to return and no wait stands between the MFMAs.  One barrier per
+// stage, behind the wave's wait for its loads of stage t + 1 (vmcnt; loads
+// complete in order), publishes that stage.  The slot of stage t - 1 takes the
+// loads of stage t + NS - 1 after it: its reads were waited for before stage
+// t - 1's MFMAs, which every wave has issued by then, so the barrier needs no
+// wait for the reads in flight.  (With two fragment sets of one step each, a
+// drain of the reads before the barrier and the slot of stage t reloaded at
+// once, a stage took 0.50 us at 128 x 128 and 0.23 at 64 x 64, whatever NS.)
+// Each output is the MFMA chain of the other paths (stages in order, two
+// 32-wide steps each): the same bits.
+template <int FM, int FN, int NS>
+__device__ __forceinline__ void compute_part(const Params& p, const TileGeom& tg, unsigned char* lds) {
+  constexpr int TM = 32 * FM, TN = 32 * FN;
+  constexpr int LPS = FM + FN;                 // loads per wave and stage: 8 rows each
+  constexpr uint32_t SLOT = (TM + TN) * ROW_BYTES;
+  static_assert(NS >= 4 && (NS - 1) * LPS < 64, "the loads in flight must fit vmcnt");
+  static_assert(NS * SLOT <= (unsigned)RING_BYTES, "the ring must fit LDS");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int KT = (p.K + KS - 1) / KS;
+  const int rows_b = min(TN, p.N - tg.n0);
+  const i32x4 rsa = rsrc_words(p.A + (size_t)tg.m0 * p.lda, (uint32_t)tg.rows * p.lda * 2u);
+  const i32x4 rsb = rsrc_words(p.B + (size_t)(tg.b0 + tg.n0) * p.ldb, (uint32_t)rows_b * p.ldb * 2u);
+  // load side: see compute_tile_ring; the wave's A blocks start at block FM
+  // wave, its B blocks at FN wave (odd for odd FN and wave)
+  const int lrow = lane >> 3;
+  const int asw = (wave * FM) & 1, bsw = (wave * FN) & 1;
+  int lca[2], lcb[2];
+  uint32_t voa[2], vob[2];
+#pragma unroll
+  for (int par = 0; par < 2; ++par) {
+    lca[par] = (lane & 7) ^ ((lrow >> 1) | ((par ^ asw) << 2));
+    lcb[par] = (lane & 7) ^ ((lrow >> 1) | ((par ^ bsw) << 2));
+    voa[par] = (uint32_t)((wave * 8 * FM + lrow) * p.lda + lca[par] * 8) * 2u;
+    vob[par] = (uint32_t)((wave * 8 * FN + lrow) * p.ldb + lcb[par] * 8) * 2u;
+  }
+  const uint32_t lds0 = (uint32_t)(size_t)lds;
+  const uint32_t dst_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 8 * FM * ROW_BYTES);
+  const uint32_t dst_b = __builtin_amdgcn_readfirstlane(lds0 + (TM + wave * 8 * FN) * ROW_BYTES);
+  const int row_a = __builtin_amdgcn_readfirstlane(8 * p.lda * 2), row_b = __builtin_amdgcn_readfirstlane(8 * p.ldb * 2);
+  // load j of stage t into the slot at byte offset `slot` (zeros past K)
+  auto load = [&](int t, uint32_t slot, int j) {
+    const int kb = __builtin_amdgcn_readfirstlane(t * KS * 2);
+    if (j < FM) {
+      const uint32_t vo = t * KS + lca[j & 1] * 8 < p.K ? voa[j & 1] : kOOB;
+      dma_1k(dst_a + slot + j * 1024, rsa, vo, j * row_a, kb);
+    } else {
+      const int i = j - FM;
+      const uint32_t vo = t * KS + lcb[i & 1] * 8 < p.K ? vob[i & 1] : kOOB;
+      dma_1k(dst_b + slot + i * 1024, rsb, vo, i * row_b, kb);
+    }
+  };
+  // read side
+  const int rrow = lane & 15;
+  uint32_t ra[2], rb[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int pchunk = ((lane >> 4) | (h << 2)) ^ ((rrow >> 1) & 7);
+    ra[h] = (uint32_t)((wm * 16 * FM + rrow) * ROW_BYTES + pchunk * 16);
+    rb[h] = (uint32_t)((TM + wn * 16 * FN + rrow) * ROW_BYTES + pchunk * 16);
+  }
+  f32x4 acc[FN][FM];
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  mfma_fence();
+  // the fragments of one stage: both 32-wide steps
+  struct Frags {
+    bf16x8 a[2][FM], b[2][FN];
+  };
+  // read i of a stage's 2 LPS, in the order the MFMAs use them
+  auto read = [&](Frags& f, uint32_t slot, int i) {
+    const int h = i / LPS, e = i % LPS;
+    if (e < FN)
+      f.b[h][e] = *reinterpret_cast<const bf16x8*>(lds + slot + rb[h] + e * 16 * ROW_BYTES);
+    else
+      f.a[h][e - FN] = *reinterpret_cast<const bf16x8*>(lds + slot + ra[h] + (e - FN) * 16 * ROW_BYTES);
+  };
+  Frags f0, f1;
+  // Stage t, its fragments in `cur`: publish stage t + 1, then the MFMAs with
+  // the reads of stage t + 1 (into `nxt`) and the loads of stage t + NS - 1
+  // spread between them.  `sn` is the slot of stage t + 1, `sl` that of t - 1.
+  auto stage = [&](int t, const Frags& cur, Frags& nxt, uint32_t sn, uint32_t sl) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 3) * LPS) : "memory");
+    constexpr int N = FM * FN;
+#pragma unroll
+    for (int q = 0; q < 2 * N; ++q) {
+      const int h = q / N, i = (q % N) / FM, j = q % FM;
+      if (h == 0) {
+#pragma unroll
+        for (int e = q * 2 * LPS / N; e < (q + 1) * 2 * LPS / N; ++e) read(nxt, sn, e);
+      }
+      mfma_acc(acc[i][j], cur.b[h][i], cur.a[h][j]);
+#pragma unroll
+      for (int e = 0; e < LPS; ++e)
+        if (q == e * 2 * N / LPS) load(t + NS - 1, sl, e);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  constexpr uint32_t RING = NS * SLOT;
+  auto after = [](uint32_t slot) { return slot + SLOT == RING ? 0u : slot + SLOT; };
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) load(t, t * SLOT, j);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LPS) : "memory");
+#pragma unroll
+  for (int e = 0; e < 2 * LPS; ++e) read(f0, 0, e);
+  uint32_t sl = RING - SLOT, sc = 0, sn = SLOT;  // slots of stages t - 1, t, t + 1
+  int t = 0;
+  for (; t + 1 < KT; t += 2) {
+    stage(t, f0, f1, sn, sl);
+    const uint32_t s2 = after(sn);
+    stage(t + 1, f1, f0, s2, sc);
+    sl = sn;
+    sc = s2;
+    sn = after(s2);
+  }
+  if (t < KT) stage(t, f0, f1, sn, sl);
+  // the zero fills still in flight land before the slots are used again, and
+  // every wave is past its last read
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+  lds_barrier();
+
+  // epilogue: blocks 2q and 2q + 1 paired as in compute_tile_ring, so a lane
+  // stores 8 consecutive columns; an odd last block stores 4
+  const __amdgpu_buffer_rsrc_t rsc =
+      make_rsrc(p.C + (size_t)tg.m0 * p.ldc + tg.n0, (uint32_t)tg.rows * p.ldc * 2u);
+  const bool c8 = (((uintptr_t)p.C & 7u) == 0) && ((p.ldc & 3) == 0);
+  const bool c16 = (((uintptr_t)p.C & 15u) == 0) && ((p.ldc & 7) == 0);
+  const int c4 = lane >> 4;
+  const int left = p.N - tg.n0;  // columns of the product from the part's first
+  auto store = [&](int col, int mb, const uint32_t* w, int n) {  // n = 4 or 8 columns from `col`
+    const uint32_t vo = (uint32_t)((wm * 16 * FM + mb * 16 + rrow) * p.ldc + col) * 2u;
+    if (c16 && n == 8 && col + 8 <= left) {
+      __builtin_amdgcn_raw_buffer_store_b128(v4u{w[0], w[1], w[2], w[3]}, rsc, vo, 0, 0);
+    } else if (c8 && col + n <= left) {
+      for (int e = 0; e < n / 4; ++e)
+        __builtin_amdgcn_raw_buffer_store_b64(v2u{w[2 * e], w[2 * e + 1]}, rsc, vo + 8u * e, 0, 0);
+    } else {
+      for (int e = 0; e < n; ++e)
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(w[e >> 1] >> (16 * (e & 1))), rsc,
+                                              col + e < left ? vo + 2u * e : kOOB, 0, 0);
+    }
+  };
+  // the accumulators leave their AGPRs from here on only
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) asm volatile("" : "+a"(acc[i][j]));
+#pragma unroll
+  for (int mb = 0; mb < FM; ++mb) {
+#pragma unroll
+    for (int q = 0; q < FN / 2; ++q) {
+      const f32x4 v = acc[2 * q][mb], u = acc[2 * q + 1][mb];
+      const auto s0 = __builtin_amdgcn_permlane16_swap(pack_bf16x2(v[0], v[1]), pack_bf16x2(u[0], u[1]), false, false);
+      const auto s1 = __builtin_amdgcn_permlane16_swap(pack_bf16x2(v[2], v[3]), pack_bf16x2(u[2], u[3]), false, false);
+      const uint32_t w[4] = {s0[0], s1[0], s0[1], s1[1]};
+      store(wn * 16 * FN + 32 * q + (c4 & 1) * 16 + (c4 >> 1) * 8, mb, w, 8);
+    }
+    if constexpr (FN & 1) {
+      const f32x4 v = acc[FN - 1][mb];
+      const uint32_t w[2] = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      store(wn * 16 * FN + (FN - 1) * 16 + c4 * 4, mb, w, 4);
+    }
+  }
+}
+
 // Another XCD's tile for a workgroup whose own region is exhausted (dynamic
 // aware mapping), so every tile is computed whatever the hardware's placement
 // of workgroups.  Run by all 64 lanes of wave 0: lane y reads XCD y's counter,
 // so one round trip shows which regions still have tiles; those are then
 // claimed from in turn, starting after the own XCD.  `q_lane` is region y's
-// tile count in lane y.  Returns -1 when every region is exhausted.
+// tile count in lane y.  Returns -1 when every region is exhausted.  PARTS:
+// counters and counts are of parts, and so is the result (tile x parts + part).
+template <bool PARTS>
 __device__ __forceinline__ int steal_aware(const Params& p, int xcc, int q_lane) {
   const int lane = threadIdx.x & 63;
   int left = 0;
@@ -745,7 +950,10 @@ __device__ __forceinline__ int steal_aware(const Params& p, int xcc, int q_lane)
     if (lane == 0) t = atomicAdd(&p.ctr[16 + y], 1);
     t = __builtin_amdgcn_readfirstlane(t);
     const int q = __builtin_amdgcn_readfirstlane(__shfl(q_lane, y));
-    if (t < q) return __builtin_amdgcn_readfirstlane(p.order[p.off[y] + t]);
+    if (t < q) {
+      if constexpr (PARTS) return part_item(p, p.off[y], t);
+      return __builtin_amdgcn_readfirstlane(p.order[p.off[y] + t]);
+    }
     open &= ~(1ull << y);
   }
   return -1;
@@ -905,13 +1113,118 @@ gemm_bf16_persistent(Params p) {
   }
 }
 
+// The part path's workgroups: assigned like gemm_bf16_persistent's (static per
+// XCD, claims on uneven CU sets and under a whole-XCD restriction, or the whole
+// order for the oblivious mappings), with a tile's parts as the unit.
+template <int FM, int FN, int NS, bool TRACE>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_bf16_parts(Params p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * 32 * (FM + FN) * ROW_BYTES];
+  int* const box = reinterpret_cast<int*>(lds);  // broadcast, used between parts only
+  const unsigned long long t_start = TRACE ? wall_clock() : 0ull;
+  const unsigned long long c_start = TRACE ? core_clock() : 0ull;
+  const int lane = threadIdx.x & 63;
+  const bool aware = p.mapping == ASYM_MAP_AWARE;
+  const bool dyn = aware && p.dynamic;
+  int base = 0, i = blockIdx.x, step = gridDim.x, end = p.n_tiles * p.parts;  // oblivious
+  int xcc = 0, own = 0, q_lane = 0;
+  if (dyn) {
+    uint32_t xr;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xr));
+    xcc = (int)(xr & 0xFu);
+    own = xcc < p.n_xccs ? xcc : 0;
+    base = __builtin_amdgcn_readfirstlane(p.off[own]);
+    end = __builtin_amdgcn_readfirstlane(p.off[own + 1] - base) * p.parts;
+    q_lane = lane < p.n_xccs ? (p.off[lane + 1] - p.off[lane]) * p.parts : 0;
+  } else if (aware) {
+    const int x = (int)blockIdx.x % p.n_xccs;
+    i = (int)blockIdx.x / p.n_xccs;
+    step = p.slots[x];
+    if (i >= step) {  // the whole workgroup, before any barrier
+      if constexpr (TRACE) trace_record(p, t_start, c_start, 0ull, 0, 0);
+      return;
+    }
+    base = p.off[x];
+    end = (p.off[x + 1] - base) * p.parts;
+  }
+  bool active = true;
+  int claimed = 0;
+  const unsigned long long t_first = TRACE ? wall_clock() : 0ull;
+  int tiles_done = 0, parts_done = 0;
+  for (;;) {
+    int item;
+    if (dyn) {
+      if (threadIdx.x < 64) {
+        int nxt = -1;
+        if (!claimed) {  // a rank ticket first: ranks past the XCD's CU count leave
+          active = xcc < p.n_xccs && p.slots[xcc] > 0;
+          if (active) {
+            int r = 0;
+            if (lane == 0) r = atomicAdd(&p.ctr[xcc], 1);
+            active = __builtin_amdgcn_readfirstlane(r) < p.slots[xcc];
+          }
+        }
+        if (active) {
+          int idx = 0;
+          if (lane == 0) idx = atomicAdd(&p.ctr[16 + own], 1);
+          idx = __builtin_amdgcn_readfirstlane(idx);
+          nxt = idx < end ? part_item(p, base, idx) : steal_aware<true>(p, xcc, q_lane);
+        }
+        if (lane == 0) box[0] = nxt;
+      }
+      claimed = 1;
+      item = read_box(box);
+    } else {
+      item = i < end ? part_item(p, base, i) : -1;
+      i += step;
+    }
+    if (item < 0) break;
+    const int tile = item / p.parts, part = item - tile * p.parts;
+    const int pr = part / p.parts_n, pc = part - pr * p.parts_n;
+    TileGeom tg = tile_geom(p, tile, p.tile_w, p.tile_h);
+    tg.m0 += pr * 32 * FM;
+    tg.rows = min(32 * FM, tg.rows - pr * 32 * FM);
+    tg.n0 += pc * 32 * FN;
+    // a part past the product's (or the group's) last row or column is empty
+    if (tg.rows > 0 && tg.n0 < p.N) {
+      if constexpr (TRACE) ++parts_done;
+      compute_part<FM, FN, NS>(p, tg, lds);
+    }
+    if constexpr (TRACE) tiles_done += part == 0;
+  }
+  if constexpr (TRACE) trace_record(p, t_start, c_start, parts_done ? t_first : 0ull, tiles_done, parts_done > 0);
+  if (dyn && threadIdx.x == 0) {
+    // the last workgroup to leave resets the counters for the next launch
+    __threadfence();
+    const int done = atomicAdd(&p.ctr[32], 1);
+    if (done == (int)gridDim.x - 1) {
+      for (int c = 0; c < 33; ++c) atomicExch(&p.ctr[c], 0);
+      __threadfence();
+    }
+  }
+}
+
 template <bool TRACE>
 int launch_gemm_kind(const GemmLaunch& g, const Params& p, hipStream_t s) {
-  if (g.bm == 128 && g.bn == 128) {
-    if (g.vec)
-      hipLaunchKernelGGL((gemm_bf16_persistent<true, 8, 128, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
+  if (g.pm) {
+    if (!g.vec) return fail(ASYM_EINVAL, "gemm: parts need the vector path");
+    const dim3 grid(g.grid), block(NT);
+    if (g.pm == 128 && g.pn == 192)
+      hipLaunchKernelGGL((gemm_bf16_parts<4, 6, 4, TRACE>), grid, block, 0, s, p);
+    else if (g.pm == 128 && g.pn == 128)
+      hipLaunchKernelGGL((gemm_bf16_parts<4, 4, 4, TRACE>), grid, block, 0, s, p);
+    else if (g.pm == 128 && g.pn == 96)
+      hipLaunchKernelGGL((gemm_bf16_parts<4, 3, 4, TRACE>), grid, block, 0, s, p);
+    else if (g.pm == 128 && g.pn == 64)
+      hipLaunchKernelGGL((gemm_bf16_parts<4, 2, 6, TRACE>), grid, block, 0, s, p);
+    else if (g.pm == 64 && g.pn == 64)
+      hipLaunchKernelGGL((gemm_bf16_parts<2, 2, 6, TRACE>), grid, block, 0, s, p);
     else
-      hipLaunchKernelGGL((gemm_bf16_persistent<false, 8, 128, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
+      return fail(ASYM_EINVAL, "gemm: unsupported part");
+    ASYM_HIP(hipGetLastError());
+    return ASYM_OK;
+  }
+  if (!g.vec && g.bm == 128 && g.bn == 128) {
+    hipLaunchKernelGGL((gemm_bf16_persistent<false, 8, 128, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
   } else if (g.bm != 256) {
     return fail(ASYM_EINVAL, "gemm: unsupported tile height");
   } else if (!g.vec)
@@ -944,6 +1257,11 @@ int launch_gemm(const GemmLaunch& g, hipStream_t s) {
   p.dynamic = g.dynamic ? 1 : 0;
   p.desc = static_cast<const int4*>(g.d_desc);
   p.trace = static_cast<asym_wg_record*>(g.d_trace);
+  p.tile_h = g.bm;
+  p.tile_w = g.bn;
+  p.parts_n = g.pm ? g.bn / g.pn : 1;
+  p.parts = g.pm ? p.parts_n * (g.bm / g.pm) : 1;
+  if (g.pm && ((g.bm % g.pm) || (g.bn % g.pn))) return fail(ASYM_EINVAL, "gemm: parts must divide the tile");
   return g.d_trace ? launch_gemm_kind<true>(g, p, s) : launch_gemm_kind<false>(g, p, s);
 }
 

@@ -1,0 +1,80 @@
+"""GEMM tiles computed in parts (the deep-ring kernel).
+
+CPU: the compiled kernels' accumulators are neither read before the MFMA fence
+nor written too late before an MFMA, and each claim is published in its own
+loop.  GPU: every part shape at the edges of its range (K of one stage, of
+fewer and more stages than ring slots, odd and even stage counts, ragged K;
+rows and columns that leave parts empty or end inside one), element by element
+against the oracle and, on integers, bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_24270_amd as asym
+from paper_2609_24270_amd import workloads
+from tests.checks import assert_gemm_close
+from tests.test_kernel_fragments import inflight_violations, write_to_mfma_violations
+from tests.test_kernel_structure import annotate_loops, asm_of, claims_published_in_their_loop, function_body
+
+PARTS = [(4, 6, 4), (4, 4, 4), (4, 3, 4), (4, 2, 6), (2, 2, 6)]  # FM, FN, ring slots
+
+
+@pytest.fixture(scope="module")
+def part_asm(tmp_path_factory):
+    return asm_of("gemm.hip", tmp_path_factory.mktemp("asm"))
+
+
+@pytest.mark.parametrize("fm,fn,ns", PARTS)
+def test_part_kernel_hazards_and_claims(part_asm, fm, fn, ns):
+    name = f"gemm_bf16_partsILi{fm}ELi{fn}ELi{ns}ELb0E"
+    kernel = f"_ZN4asym12_GLOBAL__N_115{name}EEvNS0_6ParamsE"
+    v = inflight_violations(part_asm, kernel)
+    assert not v, f"{len(v)} accumulator accesses before the MFMA fence, e.g. {v[:4]}"
+    v = write_to_mfma_violations(part_asm, kernel)
+    assert not v, f"{len(v)} asm MFMAs too soon after an accumulator write, e.g. {v[:3]}"
+    insts = annotate_loops(function_body(part_asm, name))
+    assert claims_published_in_their_loop(
+        insts, r"^global_atomic_add v\d+, v\d+, v\d+, s\[\d+:\d+\]( offset:\d+)? sc0") >= 1
+
+
+def bits(t):
+    return t.detach().cpu().contiguous().view(torch.int16).numpy().view(np.uint16)
+
+
+# On 256 CUs: 64 x 64 parts up to 64 tiles of 128 x 128, 128 x 64 up to 128,
+# 128 x 96 while those number at most 256, else 128 x 128; 128 x 192 where half
+# of the 256-row tiles' count fits.  More than 256 rows (fewer run on the
+# small-M kernel).
+SHAPES = [
+    (257, 72, 8), (257, 200, 64), (300, 500, 72), (513, 130, 448), (321, 1000, 456),        # 64 x 64
+    (1100, 1100, 8), (1100, 1100, 328), (513, 2500, 520),                                    # 128 x 64
+    (1100, 2500, 64), (1030, 2304, 200), (700, 3700, 456),                                   # 128 x 96
+    (2048, 2048, 72), (2000, 2040, 264),                                                     # 128 x 128
+    (2100, 2500, 8), (2304, 2048, 200), (2500, 2300, 328),                                   # 128 x 192
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_parts_elementwise_and_bitwise(M, N, K):
+    dev = torch.device("cuda:0")
+    for dist in ("uniform", "int"):
+        A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M + N + K, dist=dist))
+        R, Co = oracle.gemm_bf16(bits(A), bits(B), "nk")
+        Ad, Bd = A.to(dev), B.to(dev)
+        ref = None
+        for kw in ({}, {"mapping": "oblivious_rowmajor"}, {"xcd_mask": 0x0D}):  # static, whole order, claims
+            C = torch.full((M, N + 12), 3.0, dtype=torch.bfloat16, device=dev)
+            asym.gemm(Ad, Bd, C[:, :N], **kw)
+            torch.cuda.synchronize()
+            assert torch.all(C[:, N:].cpu() == 3.0), kw  # nothing past N
+            got = bits(C[:, :N])
+            if ref is None:
+                ref = got
+                if dist == "int":
+                    assert np.array_equal(got, Co)
+                else:
+                    assert assert_gemm_close(got, R, what=f"{M}x{N}x{K}") < 5e-3
+            assert np.array_equal(got, ref), kw
