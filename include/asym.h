@@ -559,9 +559,9 @@ int asym_grouped_schedule_build(int G, const int* tiles_m, int tiles_n, int n_xc
  * synchronisation when a call needs more), and the product runs as for
  * ASYM_B_NK, so both layouts of one logical B give bitwise the same C.
  * C: [M][ldc] row-major.  Requires M, N, K >= 1,
- * lda >= K, ldc >= N; 16-byte aligned pointers with lda, ldb, K
- * multiples of 8 and ldc a multiple of 4 take the vector path, anything else a
- * slower fully predicated path.  The CU set scheduled for is the stream's CU
+ * lda >= K, ldc >= N; 16-byte aligned A and B with lda, ldb, K multiples of 8
+ * take the vector path, anything else a slower one that loads through
+ * registers.  The CU set scheduled for is the stream's CU
  * mask (hipExtStreamGetCUMask) restricted to the XCDs in xcd_mask (bit x =
  * XCD x; 0 = all); workgroups landing on other XCDs exit at once.  topo may be
  * NULL (a per-device identity probe made on first use is taken); a stream
@@ -671,7 +671,7 @@ int asym_gemm_bf16_trace(const asym_topology* topo, int M, int N, int K,
  * take tiles, per XCD and in all.  claims = 1 when the aware mapping hands
  * tiles out through per-XCD counters (CU sets with unequal XCD counts),
  * 0 when every worker walks a fixed list.  vector_path = 1 for 16-byte loads
- * into LDS, 0 for the predicated path.  Synchronous, host only.
+ * straight into LDS, 0 for loads through registers (A or B off 16-byte alignment).  Synchronous, host only.
  * Errors: as asym_gemm_bf16. */
 typedef struct asym_gemm_plan_info {
   int tile_m, tile_n;

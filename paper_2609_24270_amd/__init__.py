@@ -970,7 +970,7 @@ def gemm_plan(A=None, B=None, C=None, mapping="aware", topo: Optional[Topology] 
     """What gemm() would launch for these operands (or, given M, N, K alone,
     for dense 256-byte-aligned operands of that shape): tile shape and grid,
     workers in all and per XCD, static or claiming aware form, vector or
-    predicated path.  Launches nothing."""
+    unaligned path.  Launches nothing."""
     kn = b_layout == "kn"
     if A is not None:
         M, K = A.shape

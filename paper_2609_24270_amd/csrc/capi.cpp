@@ -228,8 +228,8 @@ struct GemmPlan {
   int device = 0;
   std::vector<int> per, slots;
   int total = 0, smax = 0;
-  bool vec = false, dynamic = false, whole = true;
-  bool vec_ab = false;  // A and B alone meet the vector-path alignment
+  bool vec = false;  // A and B are aligned for direct loads into LDS
+  bool dynamic = false, whole = true;
   int bn = 0, bm = 256, tiles_m = 0, tiles_n = 0, grid = 0;
   int pm = 0, pn = 0;  // > 0: tiles computed in parts of pm x pn
   int small_mb = 0;  // > 0: the small-M kernel with this many 16-row blocks
@@ -248,17 +248,23 @@ struct GemmPlan {
 // and 58.0 in two rounds of 128 x 128.  Where whole tiles cover more than half
 // the workers the 256-row rings stay (1.4 us per stage for 3 to 4 times the
 // outputs: 2048 x 6144 74.6 whole, 99.8 in 128 x 128).  Each output is the same
-// MFMA chain in every part, so the bits do not change.
-static void choose_parts(int M, int N, GemmPlan* P) {
+// MFMA chain in every part, so the bits do not change.  Operands the rings do
+// not take (`ring` false: A, B or C off their alignment) always run in parts:
+// with A and B loaded through registers 128 x 128 ones at most (a wider one's
+// registers do not fit): 1000 x 3001 x 1501 24.2 us, in the element-wise loads
+// it replaced 92.1; 4001 x 4001 x 4095 196 against 1009.
+static void choose_parts(int M, int N, bool ring, GemmPlan* P) {
   auto tiles = [&](int64_t h, int64_t w) { return ((M + h - 1) / h) * ((N + w - 1) / w); };
   if (P->bm == 128) {
     const int64_t t = tiles(128, 128);
     P->pm = 4 * t <= P->total ? 64 : 128;
     P->pn = 2 * t <= P->total ? 64 : 128;
-    if (P->pn == 128 && tiles(128, 96) <= P->total) P->bn = P->pn = 96;
-  } else if (2 * tiles(256, 192) <= P->total) {
+    if (P->vec && P->pn == 128 && tiles(128, 96) <= P->total) P->bn = P->pn = 96;
+  } else if (P->vec && 2 * tiles(256, 192) <= P->total) {
     P->bn = P->pn = 192;
     P->pm = 128;
+  } else if (!ring) {
+    P->pm = P->pn = 128;
   }
 }
 
@@ -285,7 +291,7 @@ std::atomic<int> g_mla_form{2};
 constexpr int kSmallMMaxRows = 256;
 
 int small_m_for(const GemmPlan& P, int max_rows, long long wgs_at_64_rows) {
-  if (!g_small_m.load() || !P.vec_ab || !P.whole || max_rows > kSmallMMaxRows) return 0;
+  if (!g_small_m.load() || !P.vec || !P.whole || max_rows > kSmallMMaxRows) return 0;
   if (max_rows <= 64) return small_m_blocks(max_rows);
   return wgs_at_64_rows <= 2ll * P.total ? 4 : 0;
 }
@@ -453,15 +459,15 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
   std::vector<int> per = cs.per, slots = cs.slots;
 
   const bool vec_ab = aligned16(A) && aligned16(B) && (K % 8 == 0) && (lda % 8 == 0) && (ldb % 8 == 0);
-  const bool vec = vec_ab && (((uintptr_t)C & 7u) == 0) && (ldc % 4 == 0);
+  // the rings store C in 8-byte words and more, the parts at any alignment
+  const bool ring = vec_ab && (((uintptr_t)C & 7u) == 0) && (ldc % 4 == 0);
   P->t = t;
   P->device = device;
   P->total = total;
   P->smax = smax;
-  P->vec = vec;
-  P->vec_ab = vec_ab;
+  P->vec = vec_ab;
   P->bm = (int)BMr;
-  P->bn = vec ? choose_tile_width(M, N, total) : (int)BNr;
+  P->bn = ring ? choose_tile_width(M, N, total) : (int)BNr;
   // A product whose 256 x 256 tiles would leave three quarters of the workers
   // idle takes 128 x 128 tiles on the register-staged path: four times the
   // tiles, at most one round (512^3: 16 tiles instead of 4).  Each output is
@@ -470,7 +476,7 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
     P->bm = 128;
     P->bn = 128;
   }
-  if (vec && small_tiles) choose_parts(M, N, P);
+  if (small_tiles || !ring) choose_parts(M, N, ring, P);
   P->tiles_m = (M + P->bm - 1) / P->bm;
   P->tiles_n = (N + P->bn - 1) / P->bn;
   P->grid = mapping == ASYM_MAP_AWARE ? t->n_xccs * smax : total;
@@ -915,6 +921,8 @@ int gemm_grouped_bf16(const asym_topology* topo_in, int G, const int* Ms, int N,
   gl.dynamic = P.dynamic;
   gl.vec = P.vec;
   gl.bn = P.bn;
+  gl.pm = P.pm;
+  gl.pn = P.pn;
   gl.d_desc = tb.desc;
   return launch_gemm(gl, stream);
 }

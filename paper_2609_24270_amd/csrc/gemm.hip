@@ -44,8 +44,8 @@
 // Part path (the same operands, too few tiles for the chip): tiles cut into
 // parts of 64x64 to 128x192, one workgroup each, through a deeper ring.
 //
-// Generic path (any alignment or K): 256x256 or 128x128 tiles, k-stages of 64,
-// register-staged element loads into two padded LDS stages.
+// Operands of any alignment or K: the same parts, their rows loaded through
+// registers with 16-byte loads at any address.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -55,9 +55,8 @@
 namespace asym {
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64, NT = 256;
-constexpr int LDP = BK + 8;  // padded LDS row pitch, in bf16 elements
-constexpr int WM = 128, WN = 128;
+constexpr int BM = 256, BN = 256, NT = 256;
+constexpr int WM = 128;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -126,150 +125,9 @@ constexpr uint32_t kOOB = 0x80000000u;  // an offset past any range used here
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-// Load one 256x64 k-slice of a K-contiguous operand into registers: thread t
-// covers rows t/8 + 32*i, 16-byte chunk t%8.  `rs` spans the tile's rows
-// (rows past the matrix edge are outside it and read as zero); chunks at
-// k >= K are sent out of range as well.  The per-thread part of the offset is
-// one VGPR (`vo`, row t/8 and chunk t%8 at k = 0); the row-block and k parts
-// are uniform and go in the scalar offset.
-template <bool VEC, int NR = 8>
-__device__ __forceinline__ void load_tile(uint4 (&r)[NR], __amdgpu_buffer_rsrc_t rs, int ld,
-                                          uint32_t vo, int K, int k0) {
-  const int kc = (threadIdx.x & 7) * 8;
-  if constexpr (VEC) {
-    const uint32_t v = k0 + kc < K ? vo : kOOB;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int so = (32 * i * ld + k0) * 2;
-      const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rs, v, so, 0);
-      r[i] = make_uint4(x.x, x.y, x.z, x.w);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int so = (32 * i * ld + k0) * 2;
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = k0 + kc + 2 * e;
-        const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(rs, k < K ? vo + 4u * e : kOOB, so, 0);
-        const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(rs, k + 1 < K ? vo + 4u * e + 2u : kOOB, so, 0);
-        w[e] = lo | (hi << 16);
-      }
-      r[i] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-  }
-}
-
-template <int NR = 8>
-__device__ __forceinline__ void store_tile(uint16_t* __restrict__ s, const uint4 (&r)[NR]) {
-  const int t = threadIdx.x;
-  const int kc = (t & 7) * 8;
-#pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int row = (t >> 3) + 32 * i;
-    *reinterpret_cast<uint4*>(s + row * LDP + kc) = r[i];
-  }
-}
-
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   bf16x2 v = {(__bf16)a, (__bf16)b};
   return __builtin_bit_cast(uint32_t, v);
-}
-
-// Register-staged path: tiles TE x TE (TE = 256, or 128 for products too
-// small to give every CU a 256-wide tile), 4 waves of TE/2 x TE/2, k-stages
-// of 64 in two padded LDS buffers.  Each output is the same chain of MFMAs as
-// on the vector path (k-stages in order, two 32-wide steps each), so every
-// tile size gives the same bits.
-template <bool VEC, int TE = 256>
-__device__ __forceinline__ void compute_tile(const Params& p, int tile, uint16_t* sA, uint16_t* sB) {
-  constexpr int TW = TE / 2;      // per-wave rows and columns
-  constexpr int FR = TW / 16;     // fragments per wave and dimension
-  constexpr int NR = TE / 32;     // rows per thread in the tile loads
-  const TileGeom tg = tile_geom(p, tile, TE, TE);
-  const int m0 = tg.m0, n0 = tg.n0;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int KT = (p.K + BK - 1) / BK;
-
-  f32x4 acc[FR][FR];
-#pragma unroll
-  for (int i = 0; i < FR; ++i)
-#pragma unroll
-    for (int j = 0; j < FR; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int rows_a = tg.rows, rows_b = min(TE, p.N - n0);
-  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(p.A + (size_t)m0 * p.lda, (uint32_t)rows_a * p.lda * 2u);
-  const __amdgpu_buffer_rsrc_t rsb =
-      make_rsrc(p.B + (size_t)(tg.b0 + n0) * p.ldb, (uint32_t)rows_b * p.ldb * 2u);
-  const uint32_t voa = (uint32_t)((threadIdx.x >> 3) * p.lda + (threadIdx.x & 7) * 8) * 2u;
-  const uint32_t vob = (uint32_t)((threadIdx.x >> 3) * p.ldb + (threadIdx.x & 7) * 8) * 2u;
-  uint4 ra[NR], rb[NR];
-  load_tile<VEC, NR>(ra, rsa, p.lda, voa, p.K, 0);
-  load_tile<VEC, NR>(rb, rsb, p.ldb, vob, p.K, 0);
-  store_tile<NR>(sA, ra);
-  store_tile<NR>(sB, rb);
-  __syncthreads();
-
-  const int lrow = lane & 15, lk = (lane >> 4) * 8;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < KT;
-    if (more) {
-      load_tile<VEC, NR>(ra, rsa, p.lda, voa, p.K, (kt + 1) * BK);
-      load_tile<VEC, NR>(rb, rsb, p.ldb, vob, p.K, (kt + 1) * BK);
-    }
-    const uint16_t* a_s = sA + cur * (TE * LDP) + (wm * TW + lrow) * LDP + lk;
-    const uint16_t* b_s = sB + cur * (TE * LDP) + (wn * TW + lrow) * LDP + lk;
-#pragma unroll
-    for (int ks = 0; ks < BK / 32; ++ks) {
-      bf16x8 xa[FR], xb[FR];
-#pragma unroll
-      for (int i = 0; i < FR; ++i) {
-        xa[i] = *reinterpret_cast<const bf16x8*>(a_s + i * 16 * LDP + ks * 32);
-        xb[i] = *reinterpret_cast<const bf16x8*>(b_s + i * 16 * LDP + ks * 32);
-      }
-#pragma unroll
-      for (int nb = 0; nb < FR; ++nb)
-#pragma unroll
-        for (int mb = 0; mb < FR; ++mb)
-          acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[nb], xa[mb], acc[nb][mb], 0, 0, 0);
-    }
-    if (more) {
-      store_tile<NR>(sA + (cur ^ 1) * (TE * LDP), ra);
-      store_tile<NR>(sB + (cur ^ 1) * (TE * LDP), rb);
-    }
-    __syncthreads();
-  }
-
-  // epilogue: lane holds C[m][n..n+3] for each (nb, mb) block; rows past M
-  // fall outside the resource and their stores are dropped
-  const int rows_c = tg.rows;
-  const __amdgpu_buffer_rsrc_t rsc = make_rsrc(p.C + (size_t)m0 * p.ldc, (uint32_t)rows_c * p.ldc * 2u);
-#pragma unroll
-  for (int nb = 0; nb < FR; ++nb) {
-    const int n = n0 + wn * TW + nb * 16 + (lane >> 4) * 4;
-#pragma unroll
-    for (int mb = 0; mb < FR; ++mb) {
-      const int ml = wm * TW + mb * 16 + lrow;
-      const f32x4 v = acc[nb][mb];
-      const uint32_t base = (uint32_t)(ml * p.ldc + n) * 2u;
-      if (VEC && n + 3 < p.N && ((((uintptr_t)p.C) & 7u) == 0) && (p.ldc % 4 == 0)) {
-        v2u w;
-        w.x = pack_bf16x2(v[0], v[1]);
-        w.y = pack_bf16x2(v[2], v[3]);
-        __builtin_amdgcn_raw_buffer_store_b64(w, rsc, base, 0, 0);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const __bf16 h = (__bf16)v[r];
-          __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, h), rsc,
-                                                n + r < p.N ? base + 2u * r : kOOB, 0, 0);
-        }
-      }
-    }
-  }
 }
 
 // ---- vector path: direct-to-LDS rings ---------------------------------------------
@@ -769,49 +627,37 @@ __device__ __forceinline__ void compute_tile_ring(const Params& pin, int tile, u
 // once, a stage took 0.50 us at 128 x 128 and 0.23 at 64 x 64, whatever NS.)
 // Each output is the MFMA chain of the other paths (stages in order, two
 // 32-wide steps each): the same bits.
-template <int FM, int FN, int NS>
+template <int FM, int FN, int NS, bool DMA>
 __device__ __forceinline__ void compute_part(const Params& p, const TileGeom& tg, unsigned char* lds) {
   constexpr int TM = 32 * FM, TN = 32 * FN;
   constexpr int LPS = FM + FN;                 // loads per wave and stage: 8 rows each
   constexpr uint32_t SLOT = (TM + TN) * ROW_BYTES;
-  static_assert(NS >= 4 && (NS - 1) * LPS < 64, "the loads in flight must fit vmcnt");
+  static_assert(DMA ? NS >= 4 && (NS - 1) * LPS < 64 : NS == 3, "the loads in flight must fit vmcnt");
   static_assert(NS * SLOT <= (unsigned)RING_BYTES, "the ring must fit LDS");
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (opaque, so that no per-lane setup is hoisted out of the parts' loop and
+  // kept live across the k-loop)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int KT = (p.K + KS - 1) / KS;
   const int rows_b = min(TN, p.N - tg.n0);
-  const i32x4 rsa = rsrc_words(p.A + (size_t)tg.m0 * p.lda, (uint32_t)tg.rows * p.lda * 2u);
-  const i32x4 rsb = rsrc_words(p.B + (size_t)(tg.b0 + tg.n0) * p.ldb, (uint32_t)rows_b * p.ldb * 2u);
+  const uint16_t* const base_a = p.A + (size_t)tg.m0 * p.lda;
+  const uint16_t* const base_b = p.B + (size_t)(tg.b0 + tg.n0) * p.ldb;
   // load side: see compute_tile_ring; the wave's A blocks start at block FM
   // wave, its B blocks at FN wave (odd for odd FN and wave)
   const int lrow = lane >> 3;
   const int asw = (wave * FM) & 1, bsw = (wave * FN) & 1;
   int lca[2], lcb[2];
-  uint32_t voa[2], vob[2];
 #pragma unroll
   for (int par = 0; par < 2; ++par) {
     lca[par] = (lane & 7) ^ ((lrow >> 1) | ((par ^ asw) << 2));
     lcb[par] = (lane & 7) ^ ((lrow >> 1) | ((par ^ bsw) << 2));
-    voa[par] = (uint32_t)((wave * 8 * FM + lrow) * p.lda + lca[par] * 8) * 2u;
-    vob[par] = (uint32_t)((wave * 8 * FN + lrow) * p.ldb + lcb[par] * 8) * 2u;
   }
   const uint32_t lds0 = (uint32_t)(size_t)lds;
-  const uint32_t dst_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 8 * FM * ROW_BYTES);
-  const uint32_t dst_b = __builtin_amdgcn_readfirstlane(lds0 + (TM + wave * 8 * FN) * ROW_BYTES);
-  const int row_a = __builtin_amdgcn_readfirstlane(8 * p.lda * 2), row_b = __builtin_amdgcn_readfirstlane(8 * p.ldb * 2);
-  // load j of stage t into the slot at byte offset `slot` (zeros past K)
-  auto load = [&](int t, uint32_t slot, int j) {
-    const int kb = __builtin_amdgcn_readfirstlane(t * KS * 2);
-    if (j < FM) {
-      const uint32_t vo = t * KS + lca[j & 1] * 8 < p.K ? voa[j & 1] : kOOB;
-      dma_1k(dst_a + slot + j * 1024, rsa, vo, j * row_a, kb);
-    } else {
-      const int i = j - FM;
-      const uint32_t vo = t * KS + lcb[i & 1] * 8 < p.K ? vob[i & 1] : kOOB;
-      dma_1k(dst_b + slot + i * 1024, rsb, vo, i * row_b, kb);
-    }
-  };
+  const uint32_t dst_a = __builtin_amdgcn_readfirstlane(wave * 8 * FM * ROW_BYTES);
+  const uint32_t dst_b = __builtin_amdgcn_readfirstlane((TM + wave * 8 * FN) * ROW_BYTES);
   // read side
   const int rrow = lane & 15;
   uint32_t ra[2], rb[2];
@@ -840,48 +686,199 @@ __device__ __forceinline__ void compute_part(const Params& p, const TileGeom& tg
       f.a[h][e - FN] = *reinterpret_cast<const bf16x8*>(lds + slot + ra[h] + (e - FN) * 16 * ROW_BYTES);
   };
   Frags f0, f1;
-  // Stage t, its fragments in `cur`: publish stage t + 1, then the MFMAs with
-  // the reads of stage t + 1 (into `nxt`) and the loads of stage t + NS - 1
-  // spread between them.  `sn` is the slot of stage t + 1, `sl` that of t - 1.
-  auto stage = [&](int t, const Frags& cur, Frags& nxt, uint32_t sn, uint32_t sl) {
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 3) * LPS) : "memory");
-    constexpr int N = FM * FN;
-#pragma unroll
-    for (int q = 0; q < 2 * N; ++q) {
-      const int h = q / N, i = (q % N) / FM, j = q % FM;
-      if (h == 0) {
-#pragma unroll
-        for (int e = q * 2 * LPS / N; e < (q + 1) * 2 * LPS / N; ++e) read(nxt, sn, e);
-      }
-      mfma_acc(acc[i][j], cur.b[h][i], cur.a[h][j]);
-#pragma unroll
-      for (int e = 0; e < LPS; ++e)
-        if (q == e * 2 * N / LPS) load(t + NS - 1, sl, e);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
+  constexpr int N = FM * FN;
   constexpr uint32_t RING = NS * SLOT;
   auto after = [](uint32_t slot) { return slot + SLOT == RING ? 0u : slot + SLOT; };
+  if constexpr (DMA) {
+    const i32x4 rsa = rsrc_words(base_a, (uint32_t)tg.rows * p.lda * 2u);
+    const i32x4 rsb = rsrc_words(base_b, (uint32_t)rows_b * p.ldb * 2u);
+    uint32_t voa[2], vob[2];
 #pragma unroll
-  for (int t = 0; t < NS - 1; ++t)
+    for (int par = 0; par < 2; ++par) {
+      voa[par] = (uint32_t)((wave * 8 * FM + lrow) * p.lda + lca[par] * 8) * 2u;
+      vob[par] = (uint32_t)((wave * 8 * FN + lrow) * p.ldb + lcb[par] * 8) * 2u;
+    }
+    const int row_a = __builtin_amdgcn_readfirstlane(8 * p.lda * 2);
+    const int row_b = __builtin_amdgcn_readfirstlane(8 * p.ldb * 2);
+    // load j of stage t into the slot at byte offset `slot` (zeros past K)
+    auto load = [&](int t, uint32_t slot, int j) {
+      const int kb = __builtin_amdgcn_readfirstlane(t * KS * 2);
+      if (j < FM) {
+        const uint32_t vo = t * KS + lca[j & 1] * 8 < p.K ? voa[j & 1] : kOOB;
+        dma_1k(lds0 + dst_a + slot + j * 1024, rsa, vo, j * row_a, kb);
+      } else {
+        const int i = j - FM;
+        const uint32_t vo = t * KS + lcb[i & 1] * 8 < p.K ? vob[i & 1] : kOOB;
+        dma_1k(lds0 + dst_b + slot + i * 1024, rsb, vo, i * row_b, kb);
+      }
+    };
+    // Stage t, its fragments in `cur`: publish stage t + 1, then the MFMAs with
+    // the reads of stage t + 1 (into `nxt`) and the loads of stage t + NS - 1
+    // spread between them.  `sn` is the slot of stage t + 1, `sl` that of t - 1.
+    auto stage = [&](int t, const Frags& cur, Frags& nxt, uint32_t sn, uint32_t sl) {
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 3) * LPS) : "memory");
 #pragma unroll
-    for (int j = 0; j < LPS; ++j) load(t, t * SLOT, j);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LPS) : "memory");
+      for (int q = 0; q < 2 * N; ++q) {
+        const int h = q / N, i = (q % N) / FM, j = q % FM;
+        if (h == 0) {
 #pragma unroll
-  for (int e = 0; e < 2 * LPS; ++e) read(f0, 0, e);
-  uint32_t sl = RING - SLOT, sc = 0, sn = SLOT;  // slots of stages t - 1, t, t + 1
-  int t = 0;
-  for (; t + 1 < KT; t += 2) {
-    stage(t, f0, f1, sn, sl);
-    const uint32_t s2 = after(sn);
-    stage(t + 1, f1, f0, s2, sc);
-    sl = sn;
-    sc = s2;
-    sn = after(s2);
+          for (int e = q * 2 * LPS / N; e < (q + 1) * 2 * LPS / N; ++e) read(nxt, sn, e);
+        }
+        mfma_acc(acc[i][j], cur.b[h][i], cur.a[h][j]);
+#pragma unroll
+        for (int e = 0; e < LPS; ++e)
+          if (q == e * 2 * N / LPS) load(t + NS - 1, sl, e);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+#pragma unroll
+    for (int t = 0; t < NS - 1; ++t)
+#pragma unroll
+      for (int j = 0; j < LPS; ++j) load(t, t * SLOT, j);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LPS) : "memory");
+#pragma unroll
+    for (int e = 0; e < 2 * LPS; ++e) read(f0, 0, e);
+    uint32_t sl = RING - SLOT, sc = 0, sn = SLOT;  // slots of stages t - 1, t, t + 1
+    int t = 0;
+    for (; t + 1 < KT; t += 2) {
+      stage(t, f0, f1, sn, sl);
+      const uint32_t s2 = after(sn);
+      stage(t + 1, f1, f0, s2, sc);
+      sl = sn;
+      sc = s2;
+      sn = after(s2);
+    }
+    if (t < KT) stage(t, f0, f1, sn, sl);
+  } else {
+    // Rows that start on any 2-byte boundary, any K.  A lane loads the same
+    // 16-byte chunk the direct path does, by a global load at whatever address
+    // it has (those take any alignment), two stages ahead of its write into the
+    // slot.  Rows past the last read the last one again (their outputs are not
+    // stored).  A chunk that crosses K, or lies past it, loads the row's last 8
+    // values instead, which are shifted down to its place, zeros behind them,
+    // when the chunk is written; a K of fewer than kFirst whole stages (it may
+    // be below 8) is loaded value by value.  Bound by the loads' round trips and
+    // their second lines (a chunk row spans two): 0.73 us a stage at 128 x 128
+    // against 0.43 direct; with two-byte loads one stage ahead it took 3.8.
+    uint32_t off[LPS];
+#pragma unroll
+    for (int j = 0; j < LPS; ++j)
+      off[j] = j < FM ? (uint32_t)(min((wave * FM + j) * 8 + lrow, tg.rows - 1) * p.lda) * 2u
+                      : (uint32_t)(min((wave * FN + j - FM) * 8 + lrow, rows_b - 1) * p.ldb) * 2u;
+    auto chunk = [&](int j) { return j < FM ? lca[j & 1] : lcb[(j - FM) & 1]; };
+    auto at = [&](int j, int k) {
+      return reinterpret_cast<const char*>(j < FM ? base_a : base_b) + (off[j] + 2u * (uint32_t)k);
+    };
+    struct Regs {
+      v4u r[LPS];
+    };
+    auto load = [&](int t, Regs& g, int j) {  // (with K >= 8)
+      __builtin_memcpy(&g.r[j], at(j, min(t * KS + chunk(j) * 8, p.K - 8)), 16);
+    };
+    constexpr int kFirst = 4;
+    auto write = [&](const Regs& g, uint32_t slot, int j) {
+      *reinterpret_cast<v4u*>(lds + slot + (j < FM ? dst_a + j * 1024 : dst_b + (j - FM) * 1024) + lane * 16) = g.r[j];
+    };
+    // the chunks of stage t that reach past K
+    auto trim = [&](int t, Regs& g) {
+#pragma unroll
+      for (int j = 0; j < LPS; ++j) {
+        const int n = t * KS + chunk(j) * 8 - (p.K - 8);  // values to drop
+        const unsigned long long lo = g.r[j].x | ((unsigned long long)g.r[j].y << 32);
+        const unsigned long long hi = g.r[j].z | ((unsigned long long)g.r[j].w << 32);
+        const int b = 16 * (n & 3);
+        // n in 1 .. 3: both halves move down; 4 .. 7: the high half is what is left
+        const unsigned long long l0 = n >= 4 ? hi >> b : b ? (lo >> b) | (hi << (64 - b)) : lo;
+        const unsigned long long h0 = n >= 4 ? 0ull : hi >> b;
+        const unsigned long long l1 = n <= 0 ? lo : n >= 8 ? 0ull : l0, h1 = n <= 0 ? hi : n >= 8 ? 0ull : h0;
+        g.r[j] = v4u{(uint32_t)l1, (uint32_t)(l1 >> 32), (uint32_t)h1, (uint32_t)(h1 >> 32)};
+      }
+    };
+    // Stage t: `g` holds the loads of stage t + 2, which go into its slot `sw`
+    // (stage t - 1's); then the loads of stage t + 4 replace them.
+    using true_t = std::integral_constant<bool, true>;
+    using false_t = std::integral_constant<bool, false>;
+    auto stage = [&](auto more, int t, const Frags& cur, Frags& nxt, Regs& g, uint32_t sn, uint32_t sw) {
+      if constexpr (!decltype(more)::value) {  // (with more stages to load, stage t + 2 ends before K)
+        if ((t + 3) * KS > p.K && t + 2 >= kFirst) trim(t + 2, g);
+      }
+      lds_barrier();  // this wave's writes of stage t + 1 are done
+#pragma unroll
+      for (int q = 0; q < 2 * N; ++q) {
+        const int h = q / N, i = (q % N) / FM, j = q % FM;
+        if (h == 0) {
+#pragma unroll
+          for (int e = q * 2 * LPS / N; e < (q + 1) * 2 * LPS / N; ++e) read(nxt, sn, e);
+        }
+        mfma_acc(acc[i][j], cur.b[h][i], cur.a[h][j]);
+#pragma unroll
+        for (int e = 0; e < LPS; ++e)
+          if (q == N / 2 + e * N / LPS) {
+            write(g, sw, e);
+            if constexpr (decltype(more)::value) load(t + kFirst, g, e);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // the first stages: 0 and 1 into their slots, 2 and 3 left in flight
+    Regs g0, g1;
+    if (p.K >= kFirst * KS) {
+#pragma unroll
+      for (int t = 0; t < kFirst; ++t) {
+        Regs& g = t & 1 ? g1 : g0;
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) {
+          if (t >= 2) write(g, (t - 2) * SLOT, j);
+          load(t, g, j);
+        }
+        // (kept in this order: the waits in the loop count the loads after a set's)
+        asm volatile("" ::: "memory");
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < kFirst; ++t) {
+        Regs& g = t & 1 ? g1 : g0;
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) {
+          if (t >= 2) write(g, (t - 2) * SLOT, j);
+          int k = t * KS + chunk(j) * 8;
+          asm volatile("" : "+v"(k)::"memory");  // one chunk at a time: nothing of it is computed ahead and kept
+          uint32_t w[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t x = *reinterpret_cast<const uint16_t*>(at(j, min(k + e, p.K - 1)));
+            w[e] = k + e < p.K ? x : 0u;
+          }
+          g.r[j] = v4u{w[0] | w[1] << 16, w[2] | w[3] << 16, w[4] | w[5] << 16, w[6] | w[7] << 16};
+        }
+      }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int e = 0; e < 2 * LPS; ++e) read(f0, 0, e);
+    uint32_t sc = 0, sn = SLOT, sw = 2 * SLOT;  // slots of stages t, t + 1, t + 2
+    int t = 0;
+    for (; t + kFirst < KT; t += 2) {
+      stage(true_t{}, t, f0, f1, g0, sn, sw);
+      stage(true_t{}, t + 1, f1, f0, g1, sw, sc);
+      const uint32_t s = sw;
+      sw = sn;
+      sn = sc;
+      sc = s;
+    }
+    // the last stages, with nothing left to load
+    for (; t + 1 < KT; t += 2) {
+      stage(false_t{}, t, f0, f1, g0, sn, sw);
+      stage(false_t{}, t + 1, f1, f0, g1, sw, sc);
+      const uint32_t s = sw;
+      sw = sn;
+      sn = sc;
+      sc = s;
+    }
+    if (t < KT) stage(false_t{}, t, f0, f1, g0, sn, sw);
   }
-  if (t < KT) stage(t, f0, f1, sn, sl);
-  // the zero fills still in flight land before the slots are used again, and
-  // every wave is past its last read
+  // what is still in flight lands before the slots are used again, the last
+  // MFMAs get their wait states, and every wave is past its last read
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
   lds_barrier();
 
@@ -889,17 +886,17 @@ __device__ __forceinline__ void compute_part(const Params& p, const TileGeom& tg
   // stores 8 consecutive columns; an odd last block stores 4
   const __amdgpu_buffer_rsrc_t rsc =
       make_rsrc(p.C + (size_t)tg.m0 * p.ldc + tg.n0, (uint32_t)tg.rows * p.ldc * 2u);
-  const bool c8 = (((uintptr_t)p.C & 7u) == 0) && ((p.ldc & 3) == 0);
   const bool c16 = (((uintptr_t)p.C & 15u) == 0) && ((p.ldc & 7) == 0);
+  uint16_t* const cbase = p.C + (size_t)tg.m0 * p.ldc + tg.n0;
   const int c4 = lane >> 4;
   const int left = p.N - tg.n0;  // columns of the product from the part's first
   auto store = [&](int col, int mb, const uint32_t* w, int n) {  // n = 4 or 8 columns from `col`
-    const uint32_t vo = (uint32_t)((wm * 16 * FM + mb * 16 + rrow) * p.ldc + col) * 2u;
+    const int row = wm * 16 * FM + mb * 16 + rrow;
+    const uint32_t vo = (uint32_t)(row * p.ldc + col) * 2u;
     if (c16 && n == 8 && col + 8 <= left) {
       __builtin_amdgcn_raw_buffer_store_b128(v4u{w[0], w[1], w[2], w[3]}, rsc, vo, 0, 0);
-    } else if (c8 && col + n <= left) {
-      for (int e = 0; e < n / 4; ++e)
-        __builtin_amdgcn_raw_buffer_store_b64(v2u{w[2 * e], w[2 * e + 1]}, rsc, vo + 8u * e, 0, 0);
+    } else if (col + n <= left) {  // rows on any 2-byte boundary: global stores take any alignment
+      if (row < tg.rows) __builtin_memcpy(reinterpret_cast<char*>(cbase) + vo, w, n * 2);
     } else {
       for (int e = 0; e < n; ++e)
         __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(w[e >> 1] >> (16 * (e & 1))), rsc,
@@ -959,19 +956,6 @@ __device__ __forceinline__ int steal_aware(const Params& p, int xcc, int q_lane)
   return -1;
 }
 
-// TE = 0: the vector path's direct-to-LDS rings (256 x 32 NBF tiles);
-// otherwise the register-staged path with TE x TE tiles.
-template <bool VEC, int NBF, int TE>
-__device__ __forceinline__ void run_tile(const Params& p, int tile, unsigned char* lds, NextTile& nt) {
-  if constexpr (TE == 0) {
-    compute_tile_ring<NBF>(p, tile, lds, nt);
-  } else {
-    compute_tile<VEC, TE>(p, tile, reinterpret_cast<uint16_t*>(lds),
-                          reinterpret_cast<uint16_t*>(lds) + 2 * TE * LDP);
-    issue_next(nt);
-  }
-}
-
 // Wave 0's value in box[0] (the first word of LDS) to every wave.  Between
 // tiles no load into LDS is in flight and no wave reads it, so the word is
 // free; the second barrier keeps the next tile's loads from overwriting it
@@ -1009,10 +993,11 @@ __device__ __forceinline__ void trace_record(const Params& p, unsigned long long
   p.trace[blockIdx.x] = r;
 }
 
+// The ring path's workgroups (256 x 32 NBF tiles; VEC and TE have one value).
 template <bool VEC, int NBF, int TE = 0, bool TRACE = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 gemm_bf16_persistent(Params p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[TE == 0 ? RING_BYTES : 2 * (2 * TE) * LDP * 2];
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[RING_BYTES];
   int* const box = reinterpret_cast<int*>(lds);  // tile broadcast, used between tiles only
   const unsigned long long t_start = TRACE ? wall_clock() : 0ull;
   const unsigned long long c_start = TRACE ? core_clock() : 0ull;
@@ -1094,7 +1079,7 @@ gemm_bf16_persistent(Params p) {
   while (tile >= 0) {
     nt.i_next += nt.step;
     if constexpr (TRACE) ++n_tiles_done;
-    run_tile<VEC, NBF, TE>(p, tile, lds, nt);
+    compute_tile_ring<NBF>(p, tile, lds, nt);
     if (threadIdx.x < 64) {
       const int nxt = take_next(p, nt, xcc, q_lane);
       if (lane == 0) box[0] = nxt;
@@ -1116,7 +1101,7 @@ gemm_bf16_persistent(Params p) {
 // The part path's workgroups: assigned like gemm_bf16_persistent's (static per
 // XCD, claims on uneven CU sets and under a whole-XCD restriction, or the whole
 // order for the oblivious mappings), with a tile's parts as the unit.
-template <int FM, int FN, int NS, bool TRACE>
+template <int FM, int FN, int NS, bool DMA, bool TRACE>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_bf16_parts(Params p) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * 32 * (FM + FN) * ROW_BYTES];
   int* const box = reinterpret_cast<int*>(lds);  // broadcast, used between parts only
@@ -1187,7 +1172,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     // a part past the product's (or the group's) last row or column is empty
     if (tg.rows > 0 && tg.n0 < p.N) {
       if constexpr (TRACE) ++parts_done;
-      compute_part<FM, FN, NS>(p, tg, lds);
+      compute_part<FM, FN, NS, DMA>(p, tg, lds);
     }
     if constexpr (TRACE) tiles_done += part == 0;
   }
@@ -1205,36 +1190,32 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
 template <bool TRACE>
 int launch_gemm_kind(const GemmLaunch& g, const Params& p, hipStream_t s) {
-  if (g.pm) {
-    if (!g.vec) return fail(ASYM_EINVAL, "gemm: parts need the vector path");
-    const dim3 grid(g.grid), block(NT);
-    if (g.pm == 128 && g.pn == 192)
-      hipLaunchKernelGGL((gemm_bf16_parts<4, 6, 4, TRACE>), grid, block, 0, s, p);
-    else if (g.pm == 128 && g.pn == 128)
-      hipLaunchKernelGGL((gemm_bf16_parts<4, 4, 4, TRACE>), grid, block, 0, s, p);
-    else if (g.pm == 128 && g.pn == 96)
-      hipLaunchKernelGGL((gemm_bf16_parts<4, 3, 4, TRACE>), grid, block, 0, s, p);
-    else if (g.pm == 128 && g.pn == 64)
-      hipLaunchKernelGGL((gemm_bf16_parts<4, 2, 6, TRACE>), grid, block, 0, s, p);
-    else if (g.pm == 64 && g.pn == 64)
-      hipLaunchKernelGGL((gemm_bf16_parts<2, 2, 6, TRACE>), grid, block, 0, s, p);
-    else
-      return fail(ASYM_EINVAL, "gemm: unsupported part");
-    ASYM_HIP(hipGetLastError());
-    return ASYM_OK;
-  }
-  if (!g.vec && g.bm == 128 && g.bn == 128) {
-    hipLaunchKernelGGL((gemm_bf16_persistent<false, 8, 128, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
-  } else if (g.bm != 256) {
-    return fail(ASYM_EINVAL, "gemm: unsupported tile height");
-  } else if (!g.vec)
-    hipLaunchKernelGGL((gemm_bf16_persistent<false, 8, 256, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
+  const dim3 grid(g.grid), block(NT);
+  auto is = [&](bool vec, int pm, int pn) { return g.vec == vec && g.pm == pm && g.pn == pn; };
+  if (is(true, 128, 192))
+    hipLaunchKernelGGL((gemm_bf16_parts<4, 6, 4, true, TRACE>), grid, block, 0, s, p);
+  else if (is(true, 128, 128))
+    hipLaunchKernelGGL((gemm_bf16_parts<4, 4, 4, true, TRACE>), grid, block, 0, s, p);
+  else if (is(true, 128, 96))
+    hipLaunchKernelGGL((gemm_bf16_parts<4, 3, 4, true, TRACE>), grid, block, 0, s, p);
+  else if (is(true, 128, 64))
+    hipLaunchKernelGGL((gemm_bf16_parts<4, 2, 6, true, TRACE>), grid, block, 0, s, p);
+  else if (is(true, 64, 64))
+    hipLaunchKernelGGL((gemm_bf16_parts<2, 2, 6, true, TRACE>), grid, block, 0, s, p);
+  else if (is(false, 128, 128))
+    hipLaunchKernelGGL((gemm_bf16_parts<4, 4, 3, false, TRACE>), grid, block, 0, s, p);
+  else if (is(false, 128, 64))
+    hipLaunchKernelGGL((gemm_bf16_parts<4, 2, 3, false, TRACE>), grid, block, 0, s, p);
+  else if (is(false, 64, 64))
+    hipLaunchKernelGGL((gemm_bf16_parts<2, 2, 3, false, TRACE>), grid, block, 0, s, p);
+  else if (!g.vec || g.pm || g.bm != 256)
+    return fail(ASYM_EINVAL, "gemm: unsupported tile or part");
   else if (g.bn == 256)
-    hipLaunchKernelGGL((gemm_bf16_persistent<true, 8, 0, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
+    hipLaunchKernelGGL((gemm_bf16_persistent<true, 8, 0, TRACE>), grid, block, 0, s, p);
   else if (g.bn == 224)
-    hipLaunchKernelGGL((gemm_bf16_persistent<true, 7, 0, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
+    hipLaunchKernelGGL((gemm_bf16_persistent<true, 7, 0, TRACE>), grid, block, 0, s, p);
   else if (g.bn == 192)
-    hipLaunchKernelGGL((gemm_bf16_persistent<true, 6, 0, TRACE>), dim3(g.grid), dim3(NT), 0, s, p);
+    hipLaunchKernelGGL((gemm_bf16_persistent<true, 6, 0, TRACE>), grid, block, 0, s, p);
   else
     return fail(ASYM_EINVAL, "gemm: unsupported tile width");
   ASYM_HIP(hipGetLastError());

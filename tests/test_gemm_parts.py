@@ -18,7 +18,8 @@ from tests.checks import assert_gemm_close
 from tests.test_kernel_fragments import inflight_violations, write_to_mfma_violations
 from tests.test_kernel_structure import annotate_loops, asm_of, claims_published_in_their_loop, function_body
 
-PARTS = [(4, 6, 4), (4, 4, 4), (4, 3, 4), (4, 2, 6), (2, 2, 6)]  # FM, FN, ring slots
+# FM, FN, ring slots, direct loads into LDS
+PARTS = [(4, 6, 4, 1), (4, 4, 4, 1), (4, 3, 4, 1), (4, 2, 6, 1), (2, 2, 6, 1), (4, 4, 3, 0), (4, 2, 3, 0), (2, 2, 3, 0)]
 
 
 @pytest.fixture(scope="module")
@@ -26,9 +27,9 @@ def part_asm(tmp_path_factory):
     return asm_of("gemm.hip", tmp_path_factory.mktemp("asm"))
 
 
-@pytest.mark.parametrize("fm,fn,ns", PARTS)
-def test_part_kernel_hazards_and_claims(part_asm, fm, fn, ns):
-    name = f"gemm_bf16_partsILi{fm}ELi{fn}ELi{ns}ELb0E"
+@pytest.mark.parametrize("fm,fn,ns,dma", PARTS)
+def test_part_kernel_hazards_and_claims(part_asm, fm, fn, ns, dma):
+    name = f"gemm_bf16_partsILi{fm}ELi{fn}ELi{ns}ELb{dma}ELb0E"
     kernel = f"_ZN4asym12_GLOBAL__N_115{name}EEvNS0_6ParamsE"
     v = inflight_violations(part_asm, kernel)
     assert not v, f"{len(v)} accumulator accesses before the MFMA fence, e.g. {v[:4]}"
@@ -54,6 +55,10 @@ SHAPES = [
     (2048, 2048, 72), (2000, 2040, 264),                                                     # 128 x 128
     (2100, 2500, 8), (2304, 2048, 200), (2500, 2300, 328),                                   # 128 x 192
 ]
+# operands on 2-byte boundaries: (M, N, K, elements each row is longer than K)
+ODD = [(1, 1, 1, 0), (17, 33, 7, 2), (300, 130, 9, 0), (70, 257, 63, 1), (300, 300, 64, 3), (200, 700, 255, 0),
+       (1100, 1101, 256, 1), (65, 1000, 257, 0), (1111, 1111, 263, 0), (2050, 1999, 319, 0), (2050, 1999, 321, 5),
+       (2500, 2301, 384, 7), (129, 515, 447, 0), (1000, 3001, 449, 0), (333, 77, 1003, 0)]
 
 
 @pytest.mark.gpu
@@ -78,3 +83,53 @@ def test_parts_elementwise_and_bitwise(M, N, K):
                 else:
                     assert assert_gemm_close(got, R, what=f"{M}x{N}x{K}") < 5e-3
             assert np.array_equal(got, ref), kw
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,pad", ODD)
+def test_unaligned_operands(M, N, K, pad):
+    """Rows of any length from any 2-byte boundary, with NaNs before the first
+    element, behind each row and behind the last one: none of them is used,
+    nothing beside C is written, and every mapping gives the oracle's bits on
+    integers."""
+    dev = torch.device("cuda:0")
+
+    def placed(x, lead):
+        r, k = x.shape
+        buf = torch.full((lead + r * (k + pad) + 8,), float("nan"), dtype=torch.bfloat16, device=dev)
+        v = buf[lead:lead + r * (k + pad)].view(r, k + pad)
+        v[:, :k] = x.to(dev)
+        return v[:, :k]
+
+    for dist in ("uniform", "int"):
+        A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M + N + K, dist=dist))
+        R, Co = oracle.gemm_bf16(bits(A), bits(B), "nk")
+        for lead, kw in ((1, {}), (3, {"mapping": "oblivious_grouped"}), (5, {"xcd_mask": 0x81})):
+            Ad, Bd = placed(A, lead), placed(B, 8 - lead)
+            cb = torch.full((lead + M * (N + pad) + 8,), 3.0, dtype=torch.bfloat16, device=dev)
+            C = cb[lead:lead + M * (N + pad)].view(M, N + pad)[:, :N]
+            assert asym.gemm_plan(Ad, Bd, C, **kw)["vector_path"] == 0
+            asym.gemm(Ad, Bd, C, **kw)
+            torch.cuda.synchronize()
+            got = bits(C)
+            C.fill_(3.0)
+            assert torch.all(cb.cpu() == 3.0), kw
+            if dist == "int":
+                assert np.array_equal(got, Co), kw
+            else:
+                assert assert_gemm_close(got, R, what=f"{M}x{N}x{K} {kw}") < 5e-3
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(700, 301, 72), (2048, 2047, 200), (2300, 2303, 136), (2600, 4003, 200)])
+def test_aligned_operands_into_unaligned_c(M, N, K):
+    """A and B on the vector path, rows of C from any 2-byte boundary."""
+    dev = torch.device("cuda:0")
+    A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M, dist="int"))
+    _, Co = oracle.gemm_bf16(bits(A), bits(B), "nk")
+    C = torch.full((M, N + 2), 3.0, dtype=torch.bfloat16, device=dev)
+    assert asym.gemm_plan(A.to(dev), B.to(dev), C[:, 1:N + 1])["vector_path"] == 1
+    asym.gemm(A.to(dev), B.to(dev), C[:, 1:N + 1])
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(C[:, 1:N + 1]), Co)
+    assert torch.all(C[:, 0].cpu() == 3.0) and torch.all(C[:, N + 1].cpu() == 3.0)
