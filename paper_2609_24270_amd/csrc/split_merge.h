@@ -6,8 +6,9 @@
 //   O = (sum_s exp(m_s - M) o_s) / L,  lse = M + log L.
 // `wpr` waves work on one row (1, 2, 4, 8 or 16, from the split count): wave
 // j of a row takes splits j, j + wpr, j + 2 wpr, ... and eight of them at a
-// time, so that many partial loads are in flight; the waves' sums are added in
-// wave order.  A row's D columns may be cut into CH chunks, one per workgroup
+// time, so that many partial loads are in flight (a ragged last group too: one
+// by one, a wave with 7 splits waited seven round trips); the waves' sums are
+// added in wave order.  A row's D columns may be cut into CH chunks, one per workgroup
 // (the grid's second dimension), so that rows with many splits are read by
 // more CUs; every workgroup of a row computes M and L the same way, and each
 // output element is summed over the same splits in the same order whatever
@@ -59,7 +60,7 @@ __device__ __forceinline__ void merge_split_rows(const float* __restrict__ part_
   constexpr int DPL = DC / 64;
   static_assert(DPL == 1 || DPL == 2 || DPL == 4 || DPL == 8, "1 to 8 values per lane");
   __shared__ float red[kMergeWaves][DC];
-  __shared__ float red_m[kMergeWaves], red_l[kMergeWaves];
+  __shared__ float red_l[kMergeWaves];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int rows_per_wg = kMergeWaves / wpr;
   const int row = blockIdx.x * rows_per_wg + wave / wpr;
@@ -70,52 +71,50 @@ __device__ __forceinline__ void merge_split_rows(const float* __restrict__ part_
   const float* ml = part_ml + (size_t)(valid ? row : 0) * n_splits * 2;
   const float* po = part_o + (size_t)(valid ? row : 0) * n_splits * D + c0;
 
-  // the row's max over every split: the lanes of a wave read 64 of its
-  // splits at a time, then the waves' maxima are combined
-  float m = -INFINITY;
-  if (valid)
-    for (int s = sub + wpr * lane; s < n_splits; s += 64 * wpr) m = fmaxf(m, ml[2 * s]);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-  if (lane == 0) red_m[wave] = m;
-  __syncthreads();
-  float M = -INFINITY;
-  for (int j = 0; j < wpr; ++j) M = fmaxf(M, red_m[lead + j]);
-
+  // The wave's first eight splits go out before anything else is waited for:
+  // a merge is a few microseconds of memory latency, and the row's max, which
+  // the weights need, would otherwise be a round trip of its own before them.
+  // Splits past the last load the last one again and are not added.
   typedef typename MergeVec<DPL>::type vrow;
+  vrow x[8];
+  float2 q[8];
+  auto load = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int s = min(s0 + u * wpr, n_splits - 1);
+      x[u] = *reinterpret_cast<const vrow*>(po + (size_t)s * D);
+      q[u] = *reinterpret_cast<const float2*>(ml + 2 * s);
+    }
+  };
+  load(sub);
+  // the row's max over every split, 256 at a time (the last one again past it)
+  float M = -INFINITY;
+  for (int s = lane; s < n_splits; s += 256) {
+    float m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m[u] = ml[2 * min(s + 64 * u, n_splits - 1)];
+    M = fmaxf(M, fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])));
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
+
   vrow acc = {};
   float L = 0.f;
-  auto load = [&](int s, vrow& x, float2& q) {
-    x = *reinterpret_cast<const vrow*>(po + (size_t)s * D);
-    q = *reinterpret_cast<const float2*>(ml + 2 * s);
-  };
-  auto add = [&](const vrow& x, float2 q) {
-    const float w = __expf(q.x - M);
-    L = fmaf(q.y, w, L);
+  for (int s0 = sub; s0 < n_splits; s0 += 8 * wpr) {
+    if (s0 != sub) load(s0);
+    // one empty asm that takes the whole batch: every load is issued before
+    // the first of them is waited for (the compiler would otherwise place
+    // each load next to its use, one memory latency per split)
+    asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]),
+                 "+v"(x[7]), "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]),
+                 "+v"(q[7]));
 #pragma unroll
-    for (int e = 0; e < DPL; ++e) vset<DPL>(acc, e, fmaf(vget<DPL>(x, e), w, vget<DPL>(acc, e)));
-  };
-  if (valid) {
-    int s = sub;
-    for (; s + 7 * wpr < n_splits; s += 8 * wpr) {
-      vrow x[8];
-      float2 q[8];
+    for (int u = 0; u < 8; ++u) {
+      if (s0 + u * wpr >= n_splits) break;
+      const float w = __expf(q[u].x - M);
+      L = fmaf(q[u].y, w, L);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) load(s + u * wpr, x[u], q[u]);
-      // one empty asm that takes the whole batch: every load is issued before
-      // the first of them is waited for (the compiler would otherwise place
-      // each load next to its use, one memory latency per split)
-      asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]),
-                   "+v"(x[7]), "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]),
-                   "+v"(q[7]));
-#pragma unroll
-      for (int u = 0; u < 8; ++u) add(x[u], q[u]);
-    }
-    for (; s < n_splits; s += wpr) {
-      vrow x0;
-      float2 q0;
-      load(s, x0, q0);
-      add(x0, q0);
+      for (int e = 0; e < DPL; ++e) vset<DPL>(acc, e, fmaf(vget<DPL>(x[u], e), w, vget<DPL>(acc, e)));
     }
   }
   if (wpr > 1) {
