@@ -31,8 +31,8 @@
 //     output is rescaled only when a head's block maximum exceeds the
 //     reference maximum by more than a fixed gap (the reference then follows;
 //     below the gap the stale reference keeps the result exact);
-//   * multiples of 64 heads run in the workgroup form instead: four waves on
-//     four head blocks share each block's rows through one LDS tile.
+//   * multiples of 64 heads run in the workgroup forms instead: four waves, each
+//     on one or two head blocks, share each block's rows through LDS tiles.
 // Each task writes its unnormalised output, max and sum (fp32); a second
 // kernel merges the splits of each (request, head) in an order fixed by the
 // split count (several waves per row when there are many splits), so the
@@ -49,6 +49,8 @@
 // land on different XCDs and each XCD gets the same share whatever its CUs.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 #include "split_merge.h"
 
@@ -63,19 +65,12 @@ constexpr int MSTEPS = MD / 32;    // 18 MFMA steps for the scores
 constexpr int VSTEPS = MV / 32;    // 16 of them cover the latent part
 constexpr int V_ROW = MV * 2 + 32;  // bytes of one token's values in the per-wave tile, padded
 constexpr int V_BYTES = MT * V_ROW;  // 16.5 KiB per wave
-constexpr int MG = 4;              // workgroup form: head blocks per workgroup, one per wave
-constexpr int MT2 = 32;            // workgroup form: tokens per block
-constexpr int K_ROW = MD * 2 + 32; // workgroup form: bytes of one token's row in the shared tile
-constexpr int K_BYTES = MT2 * K_ROW;  // 37 KiB per tile, two tiles
-constexpr int WG_CHUNKS = (MT2 * (MD / 8) + 64 * MG - 1) / (64 * MG);  // 16-byte loads per thread per block
-constexpr int KB = 6;              // workgroup form: score steps per batch of key-fragment reads
-constexpr int MG2 = 8;             // 128-head form: head blocks per workgroup, two per wave
-constexpr int T2_ROWSLOTS = K_ROW / 16;  // 16-byte slots of a tile row (72 of them data)
-constexpr int T2_DMA = 10;         // 128-head form: 1 KiB direct-to-LDS loads per wave per block
-constexpr int T2_BYTES = 4 * T2_DMA * 1024;  // 40 KiB per tile (2368 slots used), three tiles
-constexpr int T2_TILES = 3;
-constexpr int KB2 = 2;             // 128-head form: score steps per batch of key-fragment reads
-static_assert(4 * T2_DMA * 64 >= MT2 * T2_ROWSLOTS, "a block's slots must fit the loads");
+constexpr int MG = 4;              // workgroup forms: waves, each on one or two head blocks
+constexpr int MT2 = 32;            // workgroup forms: tokens per block
+constexpr int T2_GROUPS = MD / 64;   // workgroup forms: 128-byte pieces of a row
+constexpr int T2_GROUP_BYTES = MT2 * 128;  // one piece of the block's 32 rows
+constexpr int T2_BYTES = T2_GROUPS * T2_GROUP_BYTES;  // 36 KiB per tile, four tiles
+constexpr int T2_TILES = 4;
 constexpr uint32_t kMlOOB = 0x80000000u;
 constexpr int kMlClaimStride = 64;  // ints between claim counters (256-byte lines)
 
@@ -232,83 +227,44 @@ __device__ __forceinline__ void mla_pv(const unsigned char* tile, uint32_t pitch
 // the probabilities come back as the B operand of a 32-deep product whose
 // k index 8 lq + i stands for the first group's token 4 lq + i (i < 4) and
 // the second group's token 16 + 4 lq + i - 4 (i >= 4).
-// The probabilities and the statistics; `alpha` is the factor the output
-// takes when the wave's ballot of `raise` is set (exactly 1 on other lanes).
-__device__ __forceinline__ bf16x8 mla_softmax32_core(f32x4 s0, f32x4 s1, int tok0, int t1, float scale, int lq,
-                                                     float& m_run, float& l_part, float& alpha, bool& raise) {
-  float v[8];
-  float bm = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int tok = tok0 + (i < 4 ? 0 : 16) + 4 * lq + (i & 3);
-    v[i] = tok < t1 ? (i < 4 ? s0[i] : s1[i - 4]) * scale : -INFINITY;
-    bm = fmaxf(bm, v[i]);
-  }
-  bm = ml_max4(bm);
-  // bm is finite (every block has a token); the first block always raises
-  raise = bm > m_run + kRescaleGap;
-  const float m_new = raise ? bm : m_run;
-  alpha = raise ? __expf(m_run - m_new) : 1.f;
-  m_run = m_new;
-  float pr[8];
-  float ps = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    pr[i] = __expf(v[i] - m_new);
-    ps += pr[i];
-  }
-  l_part = l_part * alpha + ps;
+// In steps, so that a caller can put them between other work; `alpha` is the
+// factor the output takes when the wave's ballot of `raise` is set (exactly 1
+// on other lanes).
+struct Softmax32 {
+  float v[8], ps;
   bf16x8 pb;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) pb[i] = (__bf16)pr[i];
-  return pb;
-}
-
-__device__ __forceinline__ bf16x8 mla_softmax32(f32x4 s0, f32x4 s1, int tok0, int t1, float scale, int lq,
-                                                f32x4 (&o)[MV / 16], float& m_run, float& l_part) {
   float alpha;
   bool raise;
-  const bf16x8 pb = mla_softmax32_core(s0, s1, tok0, t1, scale, lq, m_run, l_part, alpha, raise);
-  if (__ballot(raise)) {
+  // the scaled scores, tokens from t1 on masked (only the last block has any)
+  __device__ __forceinline__ void scores(f32x4 s0, f32x4 s1, int tok0, int t1, float scale, int lq) {
 #pragma unroll
-    for (int j = 0; j < MV / 16; ++j) o[j] *= alpha;
-  }
-  return pb;
-}
-
-// O^T += V^T . P^T over a 32-token block of the shared tile with
-// v_mfma_f32_16x16x32_bf16: the A operand of lane (lr, lq) joins the
-// transposing reads of the two 16-row halves (values 16 j + lr, tokens
-// 4 lq .. 4 lq + 3 of each half), in the k order of mla_softmax32.  Batches of
-// 8 products, the next batch's 16 reads in flight while a batch runs.
-__device__ __forceinline__ void mla_pv32(const unsigned char* tile, bf16x8 pb, int lr, int lq, f32x4 (&o)[MV / 16]) {
-  const uint32_t tr0 = (uint32_t)(4 * lq + (lr >> 2)) * K_ROW + 8u * (lr & 3);
-  auto read_batch = [&](int jb, i16x4 (&a)[16]) {
+    for (int i = 0; i < 8; ++i) v[i] = (i < 4 ? s0[i] : s1[i - 4]) * scale;
+    if (tok0 + MT2 > t1) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      a[2 * u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) i16x4*)(tile + tr0 + 32u * (jb + u)));
-      a[2 * u + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) i16x4*)(tile + tr0 + 16u * K_ROW + 32u * (jb + u)));
-    }
-  };
-  i16x4 ab[2][16];
-  read_batch(0, ab[0]);
-#pragma unroll
-  for (int jb = 0; jb < MV / 16; jb += 8) {
-    i16x4 (&cur)[16] = ab[(jb / 8) & 1];
-    asm volatile("" : "+v"(cur[0]), "+v"(cur[1]), "+v"(cur[2]), "+v"(cur[3]), "+v"(cur[4]), "+v"(cur[5]),
-                 "+v"(cur[6]), "+v"(cur[7]), "+v"(cur[8]), "+v"(cur[9]), "+v"(cur[10]), "+v"(cur[11]),
-                 "+v"(cur[12]), "+v"(cur[13]), "+v"(cur[14]), "+v"(cur[15]));
-    if (jb + 8 < MV / 16) read_batch(jb + 8, ab[((jb / 8) + 1) & 1]);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(cur[2 * u], cur[2 * u + 1], 0, 1, 2, 3,
-                                                                          4, 5, 6, 7));
-      o[jb + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb, o[jb + u], 0, 0, 0);
+      for (int i = 0; i < 8; ++i) v[i] = tok0 + (i < 4 ? 0 : 16) + 4 * lq + (i & 3) < t1 ? v[i] : -INFINITY;
     }
   }
-}
+  // the block's maximum and the reference
+  __device__ __forceinline__ void reference(float& m_run) {
+    float bm = v[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) bm = fmaxf(bm, v[i]);
+    bm = ml_max4(bm);
+    // bm is finite (every block has a token); the first block always raises
+    raise = bm > m_run + kRescaleGap;
+    const float m_new = raise ? bm : m_run;
+    alpha = raise ? __expf(m_run - m_new) : 1.f;
+    m_run = m_new;
+    ps = 0.f;
+  }
+  // probability i
+  __device__ __forceinline__ void prob(int i, float m_run) {
+    const float e = __expf(v[i] - m_run);
+    ps += e;
+    pb[i] = (__bf16)e;
+  }
+  __device__ __forceinline__ void sum(float& l_part) { l_part = l_part * alpha + ps; }
+};
 
 // The 16 query rows of head block hb (rows past H_q read as zero).
 __device__ __forceinline__ void mla_load_q(const MlaParams& p, int b, int hb, int lr, int lq, bf16x8 (&qf)[MSTEPS]) {
@@ -384,108 +340,29 @@ __device__ void mla_task(const MlaParams& p, int b, int split, int hb, unsigned 
   mla_store(p, b, split, hb, lr, lq, o, m_run, l_part);
 }
 
-// ---- workgroup form: one (request, split, group of 4 head blocks) per
-// workgroup, wave w on head block 4 g + w.  Each 32-token block's rows are
-// loaded once per workgroup into a shared LDS tile (two tiles, the next
-// block's loads in flight in registers) and read by all four waves: the keys
-// as score operands (the two 16-row halves as two independent MFMA chains),
-// the values through the transposing read.  The softmax runs once per
-// 32 tokens and P.V takes 32-deep products, so this form rounds differently
-// from the wave form (16-token blocks); neither depends on the placement.
-__device__ void mla_wg_task(const MlaParams& p, int b, int split, int hg, unsigned char* __restrict__ tiles) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15, lq = lane >> 4;
-  const int t0 = split * p.split;
-  const int t1 = min(p.S, t0 + p.split);
-  const int nblk = (t1 - t0 + MT2 - 1) / MT2;
-  const int hb = hg * MG + wave;
-  const __amdgpu_buffer_rsrc_t rk = ml_rsrc(p.kv + (size_t)b * p.S * MD, (uint32_t)p.S * MD * 2u);
-  bf16x8 qf[MSTEPS];
-  mla_load_q(p, b, hb, lr, lq, qf);
-  f32x4 o[MV / 16];
-#pragma unroll
-  for (int j = 0; j < MV / 16; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_part = 0.f;
-
-  // a block is 32 rows of 72 chunks of 16 bytes; thread t carries chunks
-  // t, t + 256, ... (tokens past the split read as zero)
-  auto gload = [&](int blk, v4u (&r)[WG_CHUNKS]) {
-#pragma unroll
-    for (int e = 0; e < WG_CHUNKS; ++e) {
-      const int c = threadIdx.x + 64 * MG * e;
-      const int tok = t0 + blk * MT2 + c / (MD / 8);
-      const bool in = c < MT2 * (MD / 8) && tok < t1;
-      r[e] = __builtin_amdgcn_raw_buffer_load_b128(
-          rk, in ? (uint32_t)(tok * MD + (c % (MD / 8)) * 8) * 2u : kMlOOB, 0, 0);
-    }
-  };
-  auto swrite = [&](int buf, const v4u (&r)[WG_CHUNKS]) {
-#pragma unroll
-    for (int e = 0; e < WG_CHUNKS; ++e) {
-      const int c = threadIdx.x + 64 * MG * e;
-      if (c < MT2 * (MD / 8))
-        *reinterpret_cast<v4u*>(tiles + buf * K_BYTES + (uint32_t)(c / (MD / 8)) * K_ROW + (c % (MD / 8)) * 16u) =
-            r[e];
-    }
-  };
-  // at the top of iteration blk, tile blk % 2 holds block blk and the
-  // staging registers block blk + 1
-  v4u ra[WG_CHUNKS];
-  gload(0, ra);
-  swrite(0, ra);
-  if (nblk > 1) gload(1, ra);
-  __syncthreads();
-  for (int blk = 0; blk < nblk; ++blk) {
-    const unsigned char* tile = tiles + (blk & 1) * K_BYTES;
-    // scores of the two halves: key fragments of KB steps of both halves
-    // per batch, a batch's reads all issued (the empty asm) before the
-    // previous batch's MFMAs
-    const unsigned char* krow = tile + (uint32_t)lr * K_ROW + 16u * lq;
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-    bf16x8 kf[2][2 * KB];
-    auto kread = [&](int c0, bf16x8 (&k)[2 * KB]) {
-#pragma unroll
-      for (int c = 0; c < KB; ++c) {
-        k[2 * c] = *reinterpret_cast<const bf16x8*>(krow + 64u * (c0 + c));
-        k[2 * c + 1] = *reinterpret_cast<const bf16x8*>(krow + 16u * K_ROW + 64u * (c0 + c));
-      }
-    };
-    kread(0, kf[0]);
-#pragma unroll
-    for (int c0 = 0; c0 < MSTEPS; c0 += KB) {
-      bf16x8 (&k)[2 * KB] = kf[(c0 / KB) & 1];
-      asm volatile("" : "+v"(k[0]), "+v"(k[1]), "+v"(k[2]), "+v"(k[3]), "+v"(k[4]), "+v"(k[5]), "+v"(k[6]),
-                   "+v"(k[7]), "+v"(k[8]), "+v"(k[9]), "+v"(k[10]), "+v"(k[11]));
-      if (c0 + KB < MSTEPS) kread(c0 + KB, kf[((c0 / KB) + 1) & 1]);
-#pragma unroll
-      for (int c = 0; c < KB; ++c) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[2 * c], qf[c0 + c], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[2 * c + 1], qf[c0 + c], s1, 0, 0, 0);
-      }
-    }
-    const bf16x8 pb = mla_softmax32(s0, s1, t0 + blk * MT2, t1, p.scale, lq, o, m_run, l_part);
-    mla_pv32(tile, pb, lr, lq, o);
-    // block blk + 1 into the other tile (its last readers, block blk - 1,
-    // finished before the previous barrier), then block blk + 2's loads
-    if (blk + 1 < nblk) {
-      swrite((blk + 1) & 1, ra);
-      if (blk + 2 < nblk) gload(blk + 2, ra);
-    }
-    __syncthreads();
-  }
-  mla_store(p, b, split, hb, lr, lq, o, m_run, l_part);
-}
-
-// ---- 128-head form: one (request, split, group of 8 head blocks) per
-// workgroup, wave w on head blocks 8 g + 2 w and 8 g + 2 w + 1.  Every key
-// fragment read from the tile feeds both head blocks' score chains and every
-// joined value fragment both P.V products, half the LDS reads per head of the
-// 64-head form.  The 256 output accumulators stay in AGPRs (inline-asm
-// MFMAs, with the wait states around their VALU accesses padded explicitly);
-// the rows go from memory straight into three LDS tiles (buffer_load ... lds,
-// two blocks ahead), so no registers stage them.  Per head the operations and
-// their order are those of the 64-head form, so the bits are the same.
+// ---- workgroup forms: one (request, split, group of 4 NH head blocks) per
+// workgroup, NH (1 or 2) head blocks per wave.  The rows go from memory
+// straight into four shared LDS tiles of 32 tokens (buffer_load ... lds, two
+// blocks ahead).  Every key fragment read from a tile feeds the score chains of
+// the wave's NH head blocks and every joined value fragment their P.V products,
+// so the 128-head form (NH = 2) reads half the LDS bytes per head of the
+// 64-head form (NH = 1).  The output accumulators (128 per head block) stay in
+// AGPRs (inline-asm MFMAs, with the wait states around their VALU accesses
+// padded explicitly).  The softmax runs once per 32 tokens and P.V takes
+// 32-deep products, so these forms round differently from the wave form
+// (16-token blocks); per head both do the same operations in the same order,
+// so their bits are the same, and none depends on the placement.
+//
+// What bounds it: one wave per SIMD (NH = 2 fills its registers), so nothing
+// but the wave's own instruction stream can cover a read's or the softmax's
+// latency.  The block's P.V is therefore split around the next block's scores
+// and softmax (see below).  Whole calls, before (scores, softmax and P.V in
+// turn; NH = 1 staged its rows in registers) and now, us: NH = 2, B=64, S=32768
+// 660 and 608; B=16, S=8192, 512-token splits 64.2 and 59.0 (about 20 us of it
+// do not depend on the tokens: the launch, the queries and 67 MB of fp32
+// partials, which the merge reads in another 13); NH = 1, B=16, S=4096 47.3 and
+// 36.7, B=1, S=32768 34.0 and 28.3.  Where the products and reads are placed
+// (VA = 4 to 16, three or four tiles ahead) makes less than 1%.
 
 // buffer descriptor words (uniform) for the asm loads
 __device__ __forceinline__ i32x4 ml_rsrc_words(const void* base, uint32_t bytes) {
@@ -494,12 +371,13 @@ __device__ __forceinline__ i32x4 ml_rsrc_words(const void* base, uint32_t bytes)
                (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000};
 }
 
-// 16 bytes per lane from memory into LDS: lane L's bytes land at lds + 16 L.
-// The compiler does not see these loads; their completion is waited for
-// explicitly (ml_vmwait) before the barrier that publishes the tile.
-__device__ __forceinline__ void ml_dma16(uint32_t lds, i32x4 rs, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(lds), "v"(voff), "s"(rs)
-               : "memory", "m0");
+// 16 bytes per lane from memory (byte offset voff + soff of the buffer) into
+// LDS: lane L's bytes land at lds + 16 L.  The compiler does not see these
+// loads; their completion is waited for explicitly (ml_vmwait) before the
+// barrier that publishes the tile.
+__device__ __forceinline__ void ml_dma16(uint32_t lds, i32x4 rs, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               : : "s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void ml_vmwait() {
@@ -516,163 +394,210 @@ __device__ __forceinline__ void ml_mfma_fence() {
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 }
 // the accumulators materialised in AGPRs at this point of the program
-__device__ __forceinline__ void ml_pin(f32x4 (&o)[2][MV / 16]) {
+template <int NH>
+__device__ __forceinline__ void ml_pin(f32x4 (&o)[NH][MV / 16]) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int h = 0; h < NH; ++h)
 #pragma unroll
     for (int j = 0; j < MV / 16; ++j) asm volatile("" : "+a"(o[h][j]));
 }
 
-__device__ void mla_wg2_task(const MlaParams& p, int b, int split, int hg, unsigned char* __restrict__ tiles) {
+template <int NH>
+__device__ void mla_wg_task(const MlaParams& p, int b, int split, int hg, unsigned char* __restrict__ tiles) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int lr = lane & 15, lq = lane >> 4;
   const int t0 = split * p.split;
   const int t1 = min(p.S, t0 + p.split);
   const int nblk = (t1 - t0 + MT2 - 1) / MT2;
-  const int hb0 = hg * MG2 + 2 * wave;
+  const int hb0 = (hg * MG + wave) * NH;
   // the request's rows; a split is a multiple of 32 tokens, so only the
   // request's last block is partial and its rows past S_k read as zero
   const i32x4 rk = ml_rsrc_words(p.kv + (size_t)b * p.S * MD, (uint32_t)p.S * MD * 2u);
-  bf16x8 qf[2][MSTEPS];
-  mla_load_q(p, b, hb0, lr, lq, qf[0]);
-  mla_load_q(p, b, hb0 + 1, lr, lq, qf[1]);
-  f32x4 o[2][MV / 16];
+  bf16x8 qf[NH][MSTEPS];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int h = 0; h < NH; ++h) mla_load_q(p, b, hb0 + h, lr, lq, qf[h]);
+  f32x4 o[NH][MV / 16];
+#pragma unroll
+  for (int h = 0; h < NH; ++h)
 #pragma unroll
     for (int j = 0; j < MV / 16; ++j) o[h][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  ml_pin(o);
+  ml_pin<NH>(o);
   ml_mfma_fence();
-  float m_run[2] = {-INFINITY, -INFINITY}, l_part[2] = {0.f, 0.f};
+  float m_run[NH], l_part[NH];
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    m_run[h] = -INFINITY;
+    l_part[h] = 0.f;
+  }
 
-  // load e of this wave fills slots 64 (w + 4 e) .. + 63 of the tile; slot s
-  // is row s / 74, 16-byte chunk s % 74 (chunks 72, 73 and slots past row 31
-  // are padding and read as zero)
-  uint32_t rel[T2_DMA];
-#pragma unroll
-  for (int e = 0; e < T2_DMA; ++e) {
-    const int sl = 64 * (wave + 4 * e) + lane;
-    const int row = sl / T2_ROWSLOTS, ch = sl - row * T2_ROWSLOTS;
-    rel[e] = (row < MT2 && ch < MD / 8) ? (uint32_t)(row * MD + ch * 8) * 2u : kMlOOB;
-  }
+  // A tile is 9 pieces of 32 rows x 128 bytes; a row's 16-byte chunk c of a
+  // piece lies at chunk c ^ ((row >> 1) & 7), which spreads both the 16 rows of
+  // a key fragment and the 16 half-chunks of a transposing read over the
+  // banks.  Load g of this wave fetches piece g of rows 8 w .. 8 w + 7, eight
+  // lanes per whole 128-byte line.
+  const int drow = 8 * wave + (lane >> 3);
+  const uint32_t voff = (uint32_t)(drow * MD * 2 + ((lane & 7) ^ ((drow >> 1) & 7)) * 16);
   const uint32_t lds_base = (uint32_t)(size_t)tiles;  // a shared address's low word is its LDS address
-  const uint32_t lds0 = lds_base + 1024u * (uint32_t)wave;
-  auto dma = [&](int blk) {
-    const uint32_t base = (uint32_t)(t0 + blk * MT2) * (uint32_t)(MD * 2);
-    const uint32_t dst = lds0 + (uint32_t)(blk % T2_TILES) * (uint32_t)T2_BYTES;
-#pragma unroll
-    for (int e = 0; e < T2_DMA; ++e) ml_dma16(dst + 4096u * e, rk, rel[e] == kMlOOB ? kMlOOB : base + rel[e]);
+  auto tile_at = [&](int blk) { return (uint32_t)__builtin_amdgcn_readfirstlane((blk % T2_TILES) * T2_BYTES); };
+  // (a block past the last is loaded from an empty buffer: zeros, no traffic)
+  auto dma = [&](int blk, int g) {
+    i32x4 rs = rk;
+    rs[2] = __builtin_amdgcn_readfirstlane(blk < nblk ? rk[2] : 0);
+    const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane((t0 + blk * MT2) * (MD * 2) + g * 128);
+    ml_dma16(lds_base + tile_at(blk) + (uint32_t)(g * T2_GROUP_BYTES + wave * 1024), rs, voff, so);
   };
-  dma(0);
-  if (nblk > 1) {
-    dma(1);
-    ml_vmwait<T2_DMA>();
-  } else {
-    ml_vmwait<0>();
-  }
-  __syncthreads();
-  const uint32_t tr0 = (uint32_t)(4 * lq + (lr >> 2)) * K_ROW + 8u * (lr & 3);
-  for (int blk = 0; blk < nblk; ++blk) {
-    // block blk + 2 into the tile block blk - 1 left (every wave passed the
-    // barrier after reading it)
-    if (blk + 2 < nblk) dma(blk + 2);
-    // the tile as an LDS address, so that the constant parts of the fragment
-    // addresses fold into the instructions' offsets
-    lds_u8* tile = reinterpret_cast<lds_u8*>((size_t)(lds_base + (uint32_t)(blk % T2_TILES) * (uint32_t)T2_BYTES));
-    // scores: s[h][half] for the two head blocks and the two 16-row halves;
-    // key fragments in batches of KB2 steps of both halves, three batches
-    // deep (a batch's reads issued two batches before its MFMAs)
-    lds_u8* krow = tile + (uint32_t)lr * K_ROW + 16u * lq;
-    f32x4 sc[2][2];
+  // key fragment of step c, rows 16 half + lr: chunk 4 (c & 1) + lq of piece c / 2
+  const uint32_t kb0 = (uint32_t)(lr * 128 + (lq ^ ((lr >> 1) & 7)) * 16);
+  auto kread = [&](uint32_t tile, int c, bf16x8 (&k)[2]) {
+    lds_u8* at = reinterpret_cast<lds_u8*>((size_t)(tile + (c & 1 ? kb0 ^ 64u : kb0)));
 #pragma unroll
-    for (int h = 0; h < 2; ++h) sc[h][0] = sc[h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 kf[3][2 * KB2];
-    auto kread = [&](int c0, bf16x8 (&k)[2 * KB2]) {
+    for (int half = 0; half < 2; ++half)
+      k[half] = *reinterpret_cast<lds_bf16x8*>(at + (c >> 1) * T2_GROUP_BYTES + half * 2048);
+  };
+  // value tile j (16 values), both 16-row halves: 8 bytes of rows 4 lq + lr / 4
+  // in chunk 2 (j & 3) + (lr & 3) / 2 of piece j / 4
+  const int trow = 4 * lq + (lr >> 2);
+  const uint32_t tb0 = (uint32_t)(trow * 128 + (((lr >> 1) & 1) ^ ((trow >> 1) & 7)) * 16 + 8 * (lr & 1));
+  auto tread = [&](uint32_t tile, int j, i16x4 (&v)[2]) {
+    lds_u8* at = reinterpret_cast<lds_u8*>((size_t)(tile + (tb0 ^ (uint32_t)(32 * (j & 3)))));
 #pragma unroll
-      for (int c = 0; c < KB2; ++c) {
-        k[2 * c] = *reinterpret_cast<lds_bf16x8*>(krow + 64u * (c0 + c));
-        k[2 * c + 1] = *reinterpret_cast<lds_bf16x8*>(krow + 16u * K_ROW + 64u * (c0 + c));
-      }
-    };
-    kread(0, kf[0]);
-    kread(KB2, kf[1]);
+    for (int half = 0; half < 2; ++half)
+      v[half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          reinterpret_cast<lds_i16x4*>(at + (j >> 2) * T2_GROUP_BYTES + half * 2048));
+  };
+  // Two streams of MFMAs that need nothing of each other: the scores of block
+  // blk + 1 (18 steps of NH head blocks x two 16-row halves) and the P.V of
+  // block blk (32 value tiles x NH head blocks).  The first VA tiles go between
+  // the score steps; the rest go with the softmax of block blk + 1, whose
+  // vector instructions run while the matrix cores work on them.  Each stream's
+  // reads are issued two steps or three tiles ahead.
+  constexpr int VT = MV / 16, VA = 8, TD = 4;
+  f32x4 sc[NH][2];
+  bf16x8 pb[NH];  // block blk's probabilities
+  Softmax32 sm[NH];
+  bf16x8 kf[3][2];
+  i16x4 ab[TD][2];
+  auto pv_start = [&](uint32_t tile) {
 #pragma unroll
-    for (int c0 = 0; c0 < MSTEPS; c0 += KB2) {
-      bf16x8 (&k)[2 * KB2] = kf[(c0 / KB2) % 3];
-      static_assert(KB2 == 2, "the empty asm below names the batch's four fragments");
-      asm volatile("" : "+v"(k[0]), "+v"(k[1]), "+v"(k[2]), "+v"(k[3]));
-      if (c0 + 2 * KB2 < MSTEPS) kread(c0 + 2 * KB2, kf[((c0 / KB2) + 2) % 3]);
+    for (int j = 0; j < TD - 1; ++j) tread(tile, j, ab[j]);
+  };
+  auto pv = [&](uint32_t tile, int j) {
+    i16x4 (&v)[2] = ab[j % TD];
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]));
+    if (j + TD - 1 < VT) tread(tile, j + TD - 1, ab[(j + TD - 1) % TD]);
+    const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-      for (int c = 0; c < KB2; ++c)
+    for (int h = 0; h < NH; ++h) ml_mfma_acc(o[h][j], a, pb[h]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto score_start = [&](uint32_t tile) {
+    kread(tile, 0, kf[0]);
+    kread(tile, 1, kf[1]);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          sc[h][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[2 * c], qf[h][c0 + c], sc[h][0], 0, 0, 0);
-          sc[h][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[2 * c + 1], qf[h][c0 + c], sc[h][1], 0, 0, 0);
-        }
+    for (int h = 0; h < NH; ++h) sc[h][0] = sc[h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // (with one row load of block lblk in every other step)
+  auto score = [&](uint32_t tile, int i, int lblk) {
+    bf16x8 (&k)[2] = kf[i % 3];
+    asm volatile("" : "+v"(k[0]), "+v"(k[1]));
+    if (i + 2 < MSTEPS) kread(tile, i + 2, kf[(i + 2) % 3]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        sc[h][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[u], qf[h][i], sc[h][u], 0, 0, 0);
+    if ((i & 1) == 0) dma(lblk, i >> 1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // piece x of a block's softmax
+  constexpr int PIECES = 6 * NH;
+  static_assert(VA <= MSTEPS && PIECES <= VT - VA, "at most one tile or piece per step");
+  auto softmax = [&](int blk, int x) {
+    const int h = x / 6, y = x % 6;
+    if (y == 0)
+      sm[h].scores(sc[h][0], sc[h][1], t0 + blk * MT2, t1, p.scale, lq);
+    else if (y == 1)
+      sm[h].reference(m_run[h]);
+    else {
+      sm[h].prob(2 * y - 4, m_run[h]);
+      sm[h].prob(2 * y - 3, m_run[h]);
+      if (y == 5) sm[h].sum(l_part[h]);
     }
-    bf16x8 pb[2];
-    float alpha[2];
-    bool raise[2];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(T2_GROUPS * 2 == MSTEPS, "one row load per two score steps");
+  // block blk + 1 has landed (the loads of block blk + 2 may still be in
+  // flight), and every wave is past block blk - 1, whose tile block blk + 3
+  // takes; the output takes the factor of block blk before its P.V
+  auto publish_and_rescale = [&](bool first) {
+    ml_vmwait<T2_GROUPS>();
+    __syncthreads();
+    bool raise = false;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      pb[h] = mla_softmax32_core(sc[h][0], sc[h][1], t0 + blk * MT2, t1, p.scale, lq, m_run[h], l_part[h], alpha[h],
-                                 raise[h]);
-    if (__ballot(raise[0] || raise[1])) {
+    for (int h = 0; h < NH; ++h) {
+      pb[h] = sm[h].pb;
+      raise = raise || sm[h].raise;
+    }
+    // (the first block raises every reference, but the output is still zero)
+    if (!first && __ballot(raise)) {
       ml_mfma_fence();
       // one accumulator at a time through 4 VGPRs: each read is ordered
       // after the previous write-back by the empty asms
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < NH; ++h)
 #pragma unroll
-        for (int j = 0; j < MV / 16; ++j) {
+        for (int j = 0; j < VT; ++j) {
           asm volatile("" : "+a"(o[h][j]));
           f32x4 t = o[h][j];
           asm volatile("" : "+v"(t));
-          t *= alpha[h];
+          t *= sm[h].alpha;
           o[h][j] = t;
           asm volatile("" : "+a"(o[h][j]));
         }
+      ml_mfma_fence();
     }
-    ml_mfma_fence();
-    // P.V: batches of 4 value tiles (8 transposing reads), each joined
-    // fragment used by both head blocks; the next two batches' reads in
-    // flight while a batch's 8 MFMAs run
-    auto tread = [&](int jb, i16x4 (&a)[8]) {
+  };
+  // blocks 0 and 1 in flight, the scores of block 0 (with block 2's loads)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[2 * u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>(tile + tr0 + 32u * (jb + u)));
-        a[2 * u + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            reinterpret_cast<lds_i16x4*>(tile + tr0 + 16u * K_ROW + 32u * (jb + u)));
-      }
-    };
-    i16x4 ab[3][8];
-    tread(0, ab[0]);
-    tread(4, ab[1]);
+  for (int g = 0; g < T2_GROUPS; ++g) dma(0, g);
 #pragma unroll
-    for (int jb = 0; jb < MV / 16; jb += 4) {
-      i16x4 (&cur)[8] = ab[(jb / 4) % 3];
-      asm volatile("" : "+v"(cur[0]), "+v"(cur[1]), "+v"(cur[2]), "+v"(cur[3]), "+v"(cur[4]), "+v"(cur[5]),
-                   "+v"(cur[6]), "+v"(cur[7]));
-      if (jb + 8 < MV / 16) tread(jb + 8, ab[((jb / 4) + 2) % 3]);
+  for (int g = 0; g < T2_GROUPS; ++g) dma(1, g);
+  ml_vmwait<T2_GROUPS>();
+  __syncthreads();
+  score_start(lds_base);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(cur[2 * u], cur[2 * u + 1], 0, 1, 2, 3,
-                                                                            4, 5, 6, 7));
-        ml_mfma_acc(o[0][jb + u], a, pb[0]);
-        ml_mfma_acc(o[1][jb + u], a, pb[1]);
-      }
+  for (int i = 0; i < MSTEPS; ++i) score(lds_base, i, 2);
+#pragma unroll
+  for (int x = 0; x < PIECES; ++x) softmax(0, x);
+  int blk = 0;
+  for (; blk + 1 < nblk; ++blk) {
+    publish_and_rescale(blk == 0);
+    const uint32_t vt = lds_base + tile_at(blk), st = lds_base + tile_at(blk + 1);
+    pv_start(vt);
+    score_start(st);
+#pragma unroll
+    for (int i = 0; i < MSTEPS; ++i) {
+      score(st, i, blk + 3);
+      if ((i + 1) * VA / MSTEPS > i * VA / MSTEPS) pv(vt, i * VA / MSTEPS);
     }
-    // block blk + 1 has landed (block blk + 2's loads may still be in flight)
-    if (blk + 2 < nblk)
-      ml_vmwait<T2_DMA>();
-    else
-      ml_vmwait<0>();
-    __syncthreads();
+#pragma unroll
+    for (int j = VA; j < VT; ++j) {
+      pv(vt, j);
+      const int x = (j - VA) * PIECES / (VT - VA);
+      if ((j - VA + 1) * PIECES / (VT - VA) > x) softmax(blk + 1, x);
+    }
   }
+  publish_and_rescale(blk == 0);
+  pv_start(lds_base + tile_at(blk));
+#pragma unroll
+  for (int j = 0; j < VT; ++j) pv(lds_base + tile_at(blk), j);
+  ml_vmwait<0>();  // the last zero fills
+  // (the next task's first loads overwrite tiles other waves may still read)
+  __syncthreads();
   ml_mfma_fence();
-  mla_store(p, b, split, hb0, lr, lq, o[0], m_run[0], l_part[0]);
-  mla_store(p, b, split, hb0 + 1, lr, lq, o[1], m_run[1], l_part[1]);
+#pragma unroll
+  for (int h = 0; h < NH; ++h) mla_store(p, b, split, hb0 + h, lr, lq, o[h], m_run[h], l_part[h]);
 }
 
 __global__ void __launch_bounds__(64 * MW) mla_decode_split(MlaParams p) {
@@ -748,14 +673,15 @@ __global__ void __launch_bounds__(64 * MW) mla_decode_split(MlaParams p) {
 // with the group fastest (aware) or group major (oblivious).  Oblivious: task
 // i on workgroup i.  Aware: claims of one task, own share first, then the
 // others, as in the wave form.
+// FORM: head blocks per wave.
 template <int FORM>
-__global__ void __launch_bounds__(256) mla_decode_split_wg(MlaParams p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char tiles[FORM == 2 ? T2_TILES * T2_BYTES : 2 * K_BYTES];
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) mla_decode_split_wg(MlaParams p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char tiles[T2_TILES * T2_BYTES];
   __shared__ int box[1];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const bool aware = p.quota_off != nullptr;
-  const int groups = p.hblocks / (FORM == 2 ? MG2 : MG);
+  const int groups = p.hblocks / (MG * FORM);
   int own = 0;
   if (aware) {
     uint32_t xr;
@@ -811,10 +737,7 @@ __global__ void __launch_bounds__(256) mla_decode_split_wg(MlaParams p) {
       split = r % p.n_splits;
       b = r / p.n_splits;
     }
-    if constexpr (FORM == 2)
-      mla_wg2_task(p, b, split, hg, tiles);
-    else
-      mla_wg_task(p, b, split, hg, tiles);
+    mla_wg_task<FORM>(p, b, split, hg, tiles);
   }
 }
 
@@ -877,6 +800,6 @@ int launch_mla_decode(const MlaLaunch& a, hipStream_t s) {
 
 int mla_tasks_per_workgroup() { return MW; }
 
-int mla_form_head_blocks(int form) { return form == 2 ? MG2 : form == 1 ? MG : 1; }
+int mla_form_head_blocks(int form) { return form ? MG * form : 1; }
 
 }  // namespace asym

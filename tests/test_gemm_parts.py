@@ -7,6 +7,9 @@ fewer and more stages than ring slots, odd and even stage counts, ragged K;
 rows and columns that leave parts empty or end inside one), element by element
 against the oracle and, on integers, bit for bit.
 """
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -15,7 +18,8 @@ import oracle
 import paper_2609_24270_amd as asym
 from paper_2609_24270_amd import workloads
 from tests.checks import assert_gemm_close
-from tests.test_kernel_fragments import inflight_violations, write_to_mfma_violations
+from tests.test_kernel_fragments import (CSRC, ROOT, _split, _vregs, blocks_of, inflight_violations,
+                                         write_to_mfma_violations)
 from tests.test_kernel_structure import annotate_loops, asm_of, claims_published_in_their_loop, function_body
 
 # FM, FN, ring slots, direct loads into LDS
@@ -35,9 +39,58 @@ def test_part_kernel_hazards_and_claims(part_asm, fm, fn, ns, dma):
     assert not v, f"{len(v)} accumulator accesses before the MFMA fence, e.g. {v[:4]}"
     v = write_to_mfma_violations(part_asm, kernel)
     assert not v, f"{len(v)} asm MFMAs too soon after an accumulator write, e.g. {v[:3]}"
+    v = operand_violations(part_asm, kernel)
+    assert not v, v[:4]
     insts = annotate_loops(function_body(part_asm, name))
     assert claims_published_in_their_loop(
         insts, r"^global_atomic_add v\d+, v\d+, v\d+, s\[\d+:\d+\]( offset:\d+)? sc0") >= 1
+
+
+def operand_violations(asm, kernel, min_states=2):
+    """Inline-asm MFMAs within `min_states` wait states after a compiler-placed
+    vector instruction of the same block that writes one of their A or B
+    operands (the compiler does not know the asm to be an MFMA)."""
+    out = []
+    for b in blocks_of(asm, kernel):
+        recent = {}  # VGPR -> wait states since a vector instruction wrote it
+        for inst, is_asm in b["insts"]:
+            mn, writes, _ = _split(inst)
+            if is_asm and mn.startswith("v_mfma"):
+                a, bb = (x.strip() for x in inst.split(None, 1)[1].split("],", 3)[1:3])
+                hit = [r for r in _vregs(a + "]") | _vregs(bb + "]") if recent.get(r, 99) < min_states]
+                if hit:
+                    out.append((b["label"], inst, hit))
+            step = int(inst.split()[1]) + 1 if mn == "s_nop" else 1
+            recent = {r: n + step for r, n in recent.items() if n + step < min_states}
+            if not is_asm and mn.startswith("v_") and not mn.startswith("v_mfma"):
+                recent.update({r: 0 for r in writes})
+    return out
+
+
+def test_operand_rule_sees_a_planted_write():
+    bad = "k:\n; %bb.0:\n\tv_mov_b32_e32 v5, v9\n\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]\n\t;;#ASMEND\n.Lfunc_end0:\n"
+    assert operand_violations(bad, "k")
+    assert not operand_violations(bad.replace("\t;;#ASMSTART", "\ts_nop 7\n\t;;#ASMSTART", 1), "k")
+
+
+@pytest.mark.parametrize("form", [1, 2])
+def test_latent_attention_workgroup_forms_hazards(tmp_path, form):
+    asm = _asm_vgpr_form("mla_decode.hip", tmp_path)
+    kernel = f"_ZN4asym12_GLOBAL__N_119mla_decode_split_wgILi{form}EEEvNS0_9MlaParamsE"
+    assert not inflight_violations(asm, kernel)
+    assert not write_to_mfma_violations(asm, kernel)
+    v = operand_violations(asm, kernel)
+    assert not v, v[:4]
+
+
+def _asm_vgpr_form(src, tmp_path):
+    out = tmp_path / "k.s"
+    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-I", os.path.join(ROOT, "include"),
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form=1",
+           "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return out.read_text()
 
 
 def bits(t):
