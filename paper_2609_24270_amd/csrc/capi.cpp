@@ -148,14 +148,14 @@ int stream_cu_mask(hipStream_t s, int n_cus, uint32_t* mask) {
     (void)hipGetLastError();
     std::memset(m, 0, sizeof m);
   }
-  int pop = 0;
-  for (int b = 0; b < n_cus; ++b)
-    if ((m[b >> 5] >> (b & 31)) & 1u) {
-      mask[b >> 5] |= 1u << (b & 31);
-      ++pop;
-    }
-  if (pop == 0)  // no mask reported: the whole device
-    for (int b = 0; b < n_cus; ++b) mask[b >> 5] |= 1u << (b & 31);
+  uint32_t any = 0;
+  auto device_bits = [&](int w) {  // the word's bits that are CUs of the device
+    const int valid = std::min(32, std::max(0, n_cus - 32 * w));
+    return valid == 32 ? 0xFFFFFFFFu : (1u << valid) - 1u;
+  };
+  for (int w = 0; w < ASYM_MASK_WORDS; ++w) any |= mask[w] = m[w] & device_bits(w);
+  if (!any)  // no mask reported: the whole device
+    for (int w = 0; w < ASYM_MASK_WORDS; ++w) mask[w] = device_bits(w);
   return ASYM_OK;
 }
 

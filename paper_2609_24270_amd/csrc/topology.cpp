@@ -117,10 +117,12 @@ int check_invariants(const Topology& t) {
 int mask_counts(const Topology& t, const uint32_t* mask, std::vector<int>& per) {
   per.assign(t.n_xccs, 0);
   int pop = 0;
-  for (int b = 0; b < ASYM_MAX_CUS; ++b) {
-    if (!((mask[b >> 5] >> (b & 31)) & 1u)) continue;
-    if (b >= t.n_cus) return fail(ASYM_EINVAL, "mask: bit " + std::to_string(b) + " beyond the CU count");
-    ++pop;
+  for (int w = 0; w < ASYM_MAX_CUS / 32; ++w) {  // (word by word: every launch counts its stream's mask)
+    const int valid = std::min(32, std::max(0, t.n_cus - 32 * w));
+    const uint32_t beyond = valid == 32 ? 0u : mask[w] & ~((1u << valid) - 1u);
+    if (beyond)
+      return fail(ASYM_EINVAL, "mask: bit " + std::to_string(32 * w + __builtin_ctz(beyond)) + " beyond the CU count");
+    pop += __builtin_popcount(mask[w]);
   }
   if (pop == t.n_cus) {
     per = t.cus_per_xcd;
