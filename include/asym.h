@@ -712,9 +712,9 @@ int asym_gemm_plan(const asym_topology* topo, int M, int N, int K,
  * (row-major).  Every order gives bitwise the same result.  Each workgroup
  * computes 64 columns of C for all rows (a single unsplit row tile with fewer
  * 64-column tiles than the device has CUs takes narrower tiles, a multiple of
- * 8 columns giving about one per CU; the same bits); each of its four waves
- * streams its 16 rows of B over all of K straight into MFMA operands, with A
- * shared through LDS.  This call
+ * 8 columns giving about one per CU; the same bits); the rows of B for them
+ * and the row tile's A stream through an LDS ring, one wave computing each 16
+ * columns.  This call
  * switches the path on or off for the whole process (default on; off sends
  * such products to the persistent kernel, for comparison) and returns the
  * previous setting.  Not synchronised with launches in flight. */

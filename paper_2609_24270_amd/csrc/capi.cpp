@@ -325,10 +325,11 @@ int small_m_ksplit(int M, int N, int K, int mb, int device_cus) {
   const int steps = (K + 31) / 32;
   const int u = mb == 4 ? 4 : 8;
   // only when the column tiles leave half the CUs idle, then about two
-  // workgroups per CU in a power of two of ranges, each at least two stages
-  // (measured on the decode shapes: 96 column tiles ran 18.6 us in 2 ranges
-  // and 15.4 us in 8; 224 tiles gained nothing, a 23.8 us split kernel plus a
-  // 4.5 us reduction against 28.7 us unsplit)
+  // workgroups per CU in a power of two of ranges, each of 8 (4) k-steps or
+  // more.  Measured, weights cold, us: 16 x 2048 x 8192 (32 column tiles) 23.2
+  // unsplit, 18.6 in 2 ranges, 12.9 in 8; 32 x 4096 x 4096 (64) 14.6, 14.2 and
+  // 12.7; 32 x 6144 x 4096 (96) 15.1, 16.4 and 16.7, but resident 14.4, 13.1
+  // and 14.7.
   if (2 * tiles > device_cus) return 1;
   int ks = 1;
   while (ks < 8 && (long long)ks * tiles < 2ll * device_cus) ks *= 2;
@@ -340,10 +341,9 @@ int small_m_ksplit(int M, int N, int K, int mb, int device_cus) {
 // that minimises what the busiest CU reads: ceil(workgroups / CUs) x (the
 // tile's 16 mb rows of A + its columns of B, per k), since a CU reads at about
 // 20-24 GB/s at most.  A narrower width is taken only when that saves at least
-// 7% over 64 columns (the widest on ties; measured: 32 x 14336 x 4096, 256
-// tiles of 56 columns instead of 224 of 64, 8% less read and 4% faster;
-// 32 x 10240 x 4096 in 40 columns, 1.08x; 128 x 4096 x 4096 in 32 columns,
-// 1.25x; 128 x 14336 x 4096 in 56 columns would save 6% and ran 1.4% slower).
+// 7% over 64 columns (the widest on ties; measured, weights cold, us, 64
+// columns first: 32 x 14336 x 4096 in 56 columns, 24.2 and 23.5; 32 x 10240 x
+// 4096 in 40, 20.7 and 18.0; 128 x 4096 x 4096 in 32, 21.7 and 18.3).
 // A wave with no columns at a tile's edge computes nothing; a narrower wave is
 // the same case as the product's edge, and each output is still one wave's
 // MFMA chain over all of K: the bits do not change.
@@ -500,6 +500,14 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
   return ASYM_OK;
 }
 
+// Whether data read once per launch is loaded non-temporally: from a quarter of
+// the memory-side cache (256 MiB) on.  Measured, weights cold / resident, us:
+// 32 x 6144 x 4096 (50 MB) 17.6 / 16.9 non-temporal, 16.8 / 14.7 otherwise;
+// 32 x 14336 x 4096 (117 MB) 23.6 / 22.3 and 26.5 / 20.6; 32 groups of 20 rows,
+// 4096 x 2048 (537 MB) 91.1 and 98.1.  A program's other weights and caches
+// pass through that cache between two launches, so the cold figures count.
+static bool streams_past_cache(int64_t bytes) { return bytes >= (64ll << 20); }
+
 // The small-M launch a plan asks for (everything but the partials buffer of
 // a split K, which the caller provides).
 static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void* B, void* C, int M, int N, int K,
@@ -509,8 +517,10 @@ static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void*
   sm.M = M; sm.N = N; sm.K = K; sm.lda = lda; sm.ldb = ldb; sm.ldc = ldc;
   sm.mb = P.small_mb;
   sm.row_tiles = (M + 16 * P.small_mb - 1) / (16 * P.small_mb);
+  sm.b_once = sm.row_tiles == 1 && streams_past_cache((int64_t)N * K * 2);
   sm.order = small_m_order(mapping);
   sm.n_x = P.t->n_xccs;
+  sm.device_cus = P.t->n_cus;
   sm.ksplit = small_m_ksplit(M, N, K, P.small_mb, P.t->n_cus);
   sm.tile_cols = small_m_cols(N, P.small_mb, sm.row_tiles, sm.ksplit, P.t->n_cus);
   const int tiles_n = (N + sm.tile_cols - 1) / sm.tile_cols;
@@ -900,6 +910,8 @@ int gemm_grouped_bf16(const asym_topology* topo_in, int G, const int* Ms, int N,
     sm.M = (int)rows; sm.N = N; sm.K = K; sm.lda = lda; sm.ldb = ldb; sm.ldc = ldc;
     sm.mb = small_mb;
     sm.n_x = P.t->n_xccs;
+    sm.device_cus = P.t->n_cus;
+    sm.b_once = max_rows <= 16 * small_mb && streams_past_cache((int64_t)G * N * K * 2);
     sm.grid = T;
     sm.d_desc = tb.desc;
     sm.tile_cols = small_w;

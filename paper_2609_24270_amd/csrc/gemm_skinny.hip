@@ -5,17 +5,22 @@
 // With a few rows the work is bound by streaming B from HBM once (2 N K bytes
 // against 2 M N K flops), so the kernel is built for memory-level parallelism
 // rather than for operand reuse.  A workgroup owns a 64-column slice of C for
-// its row tile; each of its four waves owns 16 of those columns and all of K,
-// and streams its 16 B rows straight into MFMA operand registers (a lane's 8
-// bf16 of a 16x32 fragment are 16 contiguous bytes of one row), two groups of
-// U k-steps in flight.  A, the same for every wave, goes through LDS once per
-// stage of U k-steps (double-buffered, one barrier per stage), so the vector
-// memory path carries B and little else: with A loaded by every wave, one A
-// fragment load per B fragment load, the kernel streamed B at about 4 TB/s;
-// shared through LDS, close to the chip's read rate.  Each output element is
-// one wave's MFMA chain over k in order, as in the persistent kernel.  Every B
-// byte is fetched once and no tile is reused, so there is no placement to
-// choose: the grid is a plain launch over the tiles.
+// its row tile; each of its four waves owns 16 of those columns and all of K.
+// Both operands go from memory straight into an LDS ring (buffer_load ... lds)
+// in stages of 64 k, eight lanes per whole 128-byte line of a row, with NS - 1
+// stages in flight and one barrier per stage; the fragments of a stage are read
+// while the one before it is computed.  What bounds it is the rate one CU
+// streams at (20-24 GB/s from HBM) and how soon it gets there.  Before, a wave
+// loaded its B fragments straight into operand registers, 64 bytes of 16 rows
+// per load, half lines that the vector cache takes twice: 32 x 14336 x 4096
+// (weights not in any cache) 32.2 us, now 23.4 (5.0 TB/s); 64 rows 46.7, now
+// 26.6; 32 groups of 20 rows, 6144 x 7168, 495, now 419 (6.7 TB/s).  A tenth of
+// it is the cache policy: B rows that one workgroup reads alone are loaded
+// non-temporally (26.0 against 23.4 us; 464 against 419), rows that several row
+// tiles share are not (128 x 14336 x 4096 40.6 us, non-temporal 42.1).
+// Each output element is one wave's MFMA chain over k in order, as in the
+// persistent kernel.  Every B byte is fetched once and no tile is reused, so
+// there is no placement to choose: the grid is a plain launch over the tiles.
 //
 // A plain problem is cut into row tiles of 16 MB rows (one tile up to 64
 // rows); a grouped problem's workgroups each read a descriptor {first row,
@@ -34,7 +39,7 @@ namespace {
 constexpr int SK_WAVES = 4;
 constexpr int SK_THREADS = 64 * SK_WAVES;
 constexpr int SK_COLS = 16 * SK_WAVES;  // 64 columns per tile, 16 per wave
-constexpr uint32_t kSkOOB = 0x80000000u;
+constexpr uint32_t kSkOOB = 0x80000000u;  // an offset past any range used here
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -70,11 +75,40 @@ __device__ __forceinline__ uint32_t sk_pack(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// MB: 16-row blocks of the row tile (1, 2 or 4); U: k-steps of 32 per stage.
-template <int MB, int U>
+constexpr int SK_KS = 64;               // k per stage: one 128-byte line of every row
+constexpr int SK_ROW_BYTES = SK_KS * 2;
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// buffer descriptor words (uniform) for the asm loads
+__device__ __forceinline__ i32x4 sk_words(const void* base, uint32_t bytes) {
+  const unsigned long long a = (unsigned long long)base;
+  return i32x4{(int)__builtin_amdgcn_readfirstlane((uint32_t)a), (int)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
+               (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000};
+}
+
+// 16 bytes per lane (byte offset voff + soff of the buffer) into LDS: lane L's
+// land at lds + 16 L.  The compiler does not see these loads; they are waited
+// for explicitly before the barrier that publishes a stage.  NT: non-temporal.
+template <bool NT>
+__device__ __forceinline__ void sk_dma(uint32_t lds, i32x4 rs, uint32_t voff, uint32_t soff) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 : : "s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+}
+
+// MB: 16-row blocks of the row tile (1, 2 or 4); NS: ring slots; ONCE: no other
+// workgroup reads this one's B rows, and they are loaded non-temporally.
+template <int MB, int NS, bool ONCE>
 __global__ void __launch_bounds__(SK_THREADS) gemm_bf16_small_m(SkinnyParams p) {
-  // A stage in LDS, in MFMA operand order: fragment (u, i) is 64 lanes x 16 bytes
-  __shared__ bf16x8 sa[2][U * MB * 64];
+  constexpr int A_BYTES = 16 * MB * SK_ROW_BYTES;                  // a stage of A
+  constexpr uint32_t SLOT = A_BYTES + SK_COLS * SK_ROW_BYTES;      // and of B
+  constexpr int LA = MB == 4 ? 2 : 1, LPS = LA + 2;                // loads per wave and stage: 8 rows each
+  static_assert(NS >= 4 && (NS - 1) * LPS < 64, "the loads in flight must fit vmcnt");
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * SLOT];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int row0, rows, brow0, ncol0, kr = 0, ctile = 0;
@@ -115,102 +149,106 @@ __global__ void __launch_bounds__(SK_THREADS) gemm_bf16_small_m(SkinnyParams p) 
     ncol0 = c * p.tile_cols;
     ctile = c;
   }
-  // this wave's 16 columns (fewer at the tile's or the product's edge); a wave
-  // past either has an empty B range and stores nothing
+  // this wave's 16 columns (fewer, or none, at the tile's or the product's edge)
   const int n0 = ncol0 + wave * 16;
-  const int cols = max(0, min(16, min(p.N, ncol0 + p.tile_cols) - n0));
+  const int tile_cols = min(p.N - ncol0, p.tile_cols);
+  const int cols = max(0, min(16, tile_cols - wave * 16));
 
-  // rows past the tile read as zero (outside the resource); a 16-byte chunk at
-  // k >= K is sent out of range (K is a multiple of 8: a chunk is all inside
-  // or all outside)
-  const __amdgpu_buffer_rsrc_t ra = sk_rsrc(p.A + (size_t)row0 * p.lda, (uint32_t)rows * p.lda * 2u);
-  const __amdgpu_buffer_rsrc_t rb =
-      sk_rsrc(p.B + (size_t)(brow0 + min(n0, p.N)) * p.ldb, (uint32_t)cols * p.ldb * 2u);
-  const int lr = lane & 15, lk = (lane >> 4) * 8;
-  const uint32_t vob = (uint32_t)(lr * p.ldb + lk) * 2u;
   // this workgroup's k-steps of 32: all of K, or its range of a split K
   const int steps = (p.K + 31) >> 5;
   const int per = (steps + p.ksplit - 1) / p.ksplit;
   const int ks0 = min(steps, kr * per), ks1 = min(steps, ks0 + per);
-  const int stages = (ks1 - ks0 + U - 1) / U;
+  const int k0 = ks0 * 32, k1 = min(p.K, ks1 * 32);
+  const int KT = (k1 - k0 + SK_KS - 1) / SK_KS;
 
-  // A staging: chunk c of a stage is (row, k-step u, quarter kq) in row-major
-  // order; thread t carries chunks t, t + 256, ...
-  constexpr int CHUNKS = MB * 16 * U * 4;
-  constexpr int A_PER = (CHUNKS + SK_THREADS - 1) / SK_THREADS;
-  auto a_load = [&](int st, v4u (&r)[A_PER]) {
+  // Rows past the tile read as zero (outside the resource), and so does a
+  // 16-byte chunk at k >= k1 (K is a multiple of 8: a chunk is all inside or
+  // all outside).  A row's chunk c lies at chunk c ^ ((row >> 1) & 7) of its
+  // line, which keeps the 16 rows of a fragment read free of bank conflicts.
+  // Loads: wave w takes rows 16 w .. 16 w + 15 of B (its own columns) and its
+  // share of A's 2 MB blocks of 8 rows (waves 2 and 3 repeat those of 0 and 1
+  // when there are two).
+  const i32x4 ra = sk_words(p.A + (size_t)row0 * p.lda, (uint32_t)rows * p.lda * 2u);
+  const i32x4 rb = sk_words(p.B + (size_t)(brow0 + ncol0) * p.ldb, (uint32_t)tile_cols * p.ldb * 2u);
+  const int lrow = lane >> 3;
+  const int ablk = MB == 1 ? wave & 1 : MB == 2 ? wave : 2 * wave;  // the wave's first block of A
+  int ca[2], cb[2];
+  uint32_t va[2], vb[2];
 #pragma unroll
-    for (int e = 0; e < A_PER; ++e) {
-      const int c = threadIdx.x + e * SK_THREADS;
-      const int row = c / (U * 4), cc = c % (U * 4);
-      const int ks = ks0 + st * U + (cc >> 2);
-      const int k = ks * 32 + (cc & 3) * 8;
-      const bool in = c < CHUNKS && ks < ks1 && k < p.K;
-      r[e] = __builtin_amdgcn_raw_buffer_load_b128(ra, in ? (uint32_t)(row * p.lda + k) * 2u : kSkOOB, 0, 0);
-    }
+  for (int i = 0; i < 2; ++i) {
+    ca[i] = (lane & 7) ^ ((lrow >> 1) | (((ablk + i) & 1) << 2));
+    cb[i] = (lane & 7) ^ ((lrow >> 1) | (i << 2));
+    va[i] = (uint32_t)(((ablk + i) * 8 + lrow) * p.lda + ca[i] * 8) * 2u;
+    vb[i] = (uint32_t)((wave * 16 + i * 8 + lrow) * p.ldb + cb[i] * 8) * 2u;
+  }
+  const uint32_t lds0 = (uint32_t)(size_t)ring;
+  const uint32_t da = __builtin_amdgcn_readfirstlane(lds0 + ablk * 1024);
+  const uint32_t db = __builtin_amdgcn_readfirstlane(lds0 + A_BYTES + wave * 2048);
+  auto load = [&](int t, uint32_t slot) {
+    const int k = k0 + t * SK_KS;
+    const uint32_t so = __builtin_amdgcn_readfirstlane(min(k, k1) * 2);  // never past the resource's end
+#pragma unroll
+    for (int i = 0; i < 2; ++i) sk_dma<ONCE>(db + slot + i * 1024, rb, k + cb[i] * 8 < k1 ? vb[i] : kSkOOB, so);
+#pragma unroll
+    for (int i = 0; i < LA; ++i) sk_dma<false>(da + slot + i * 1024, ra, k + ca[i] * 8 < k1 ? va[i] : kSkOOB, so);
   };
-  auto a_store = [&](int buf, const v4u (&r)[A_PER]) {
+  const int lr = lane & 15;
+  uint32_t fa[2], fb[2];
 #pragma unroll
-    for (int e = 0; e < A_PER; ++e) {
-      const int c = threadIdx.x + e * SK_THREADS;
-      if (c >= CHUNKS) continue;
-      const int row = c / (U * 4), cc = c % (U * 4);
-      const int u = cc >> 2, kq = cc & 3;
-      sa[buf][(u * MB + (row >> 4)) * 64 + (row & 15) + 16 * kq] = __builtin_bit_cast(bf16x8, r[e]);
-    }
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t ch = (uint32_t)(((lane >> 4) | (h << 2)) ^ ((lr >> 1) & 7)) * 16u;
+    fa[h] = lr * SK_ROW_BYTES + ch;
+    fb[h] = A_BYTES + (wave * 16 + lr) * SK_ROW_BYTES + ch;
+  }
+  struct Frags {
+    bf16x8 a[2][MB], b[2];
   };
-  auto b_load = [&](int st, bf16x8 (&b)[U]) {
+  auto read = [&](Frags& f, uint32_t slot) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int ks = ks0 + st * U + u;
-      const int k = ks * 32;
-      const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rb, ks < ks1 && k + lk < p.K ? vob : kSkOOB, k * 2, 0);
-      b[u] = __builtin_bit_cast(bf16x8, x);
+    for (int h = 0; h < 2; ++h) {
+      f.b[h] = *reinterpret_cast<const bf16x8*>(ring + slot + fb[h]);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        f.a[h][i] = *reinterpret_cast<const bf16x8*>(ring + slot + fa[h] + i * 16 * SK_ROW_BYTES);
     }
   };
   f32x4 acc[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int buf, const bf16x8 (&b)[U]) {
+  // Stage t, its fragments in `cur`: publish stage t + 1 (this wave's loads of
+  // it have landed; loads complete in order), read it into `nxt`, reload the
+  // slot of stage t - 1 (`sl`: its reads were waited for before its MFMAs, which
+  // every wave has issued by this barrier), then the MFMAs.
+  auto stage = [&](int t, const Frags& cur, Frags& nxt, uint32_t sn, uint32_t sl) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 3) * LPS) : "memory");
+    read(nxt, sn);
+    load(t + NS - 1, sl);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      bf16x8 a[MB];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int i = 0; i < MB; ++i) a[i] = sa[buf][(u * MB + i) * 64 + lane];
-#pragma unroll
-      for (int i = 0; i < MB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[u], a[i], acc[i], 0, 0, 0);
-    }
+      for (int i = 0; i < MB; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[h], cur.a[h][i], acc[i], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
   };
-
-  // stage s uses LDS buffer s % 2 and B registers b0 (even) / b1 (odd); the
-  // loads of stage s + 1 are in flight while stage s is computed
-  // a wave with no columns (past the tile's or the product's edge) stages A
-  // and meets the barriers but loads no B and computes nothing
-  const bool busy = cols > 0;
-  bf16x8 b0[U], b1[U];
-  v4u ar[A_PER];
-  a_load(0, ar);
-  a_store(0, ar);
-  if (stages > 1) a_load(1, ar);
-  if (busy) b_load(0, b0);
-  __syncthreads();
-  for (int st = 0; st < stages; st += 2) {
-    if (busy && st + 1 < stages) b_load(st + 1, b1);
-    if (busy) compute(0, b0);
-    if (st + 1 < stages) {
-      a_store(1, ar);
-      if (st + 2 < stages) a_load(st + 2, ar);
-    }
-    __syncthreads();
-    if (st + 1 >= stages) break;
-    if (busy && st + 2 < stages) b_load(st + 2, b0);
-    if (busy) compute(1, b1);
-    if (st + 2 < stages) {
-      a_store(0, ar);
-      if (st + 3 < stages) a_load(st + 3, ar);
-    }
-    __syncthreads();
+  constexpr uint32_t RING = NS * SLOT;
+  auto after = [](uint32_t slot) { return slot + SLOT == RING ? 0u : slot + SLOT; };
+  Frags f0, f1;
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t) load(t, t * SLOT);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LPS) : "memory");
+  read(f0, 0);
+  uint32_t sl = RING - SLOT, sc = 0, sn = SLOT;  // slots of stages t - 1, t, t + 1
+  int t = 0;
+  for (; t + 1 < KT; t += 2) {
+    stage(t, f0, f1, sn, sl);
+    const uint32_t s2 = after(sn);
+    stage(t + 1, f1, f0, s2, sc);
+    sl = sn;
+    sc = s2;
+    sn = after(s2);
   }
+  if (t < KT) stage(t, f0, f1, sn, sl);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zero fills past the end land before the LDS is given back
 
   // in a 16x16 block the lane with row r = lane % 16 holds columns 4c..4c+3,
   // c = lane / 16; rows past the tile fall outside the resource
@@ -303,20 +341,33 @@ int launch_gemm_small_m(const SmallMLaunch& g, hipStream_t s) {
     return fail(ASYM_EINVAL, "small-M GEMM: a split K needs one row tile and a workspace");
   const long long grid = g.grid;
   if (grid < 1 || grid > (1ll << 31) - 1) return fail(ASYM_EINVAL, "small-M GEMM: grid out of range");
+  // One workgroup per CU at most: the ring takes most of a CU's LDS (72 to 104
+  // KiB of B in flight).  More workgroups than CUs: half of that each, so that
+  // two share a CU and one's start overlaps the other's stream (32 groups of
+  // 20 rows, 4096 x 2048: 98 us against 114 with the deep ring for all).
+  const bool deep = grid <= g.device_cus;
+#define ASYM_SMALL_M(mb, ns, once)                                                                          \
+  hipLaunchKernelGGL((gemm_bf16_small_m<mb, ns, once>), dim3((unsigned)grid), dim3(SK_THREADS), 0, s, p)
+#define ASYM_SMALL_M_CASE(mb, ns_deep, ns)                                       \
+  case mb:                                                                       \
+    if (deep && g.b_once)                                                        \
+      ASYM_SMALL_M(mb, ns_deep, true);                                           \
+    else if (deep)                                                               \
+      ASYM_SMALL_M(mb, ns_deep, false);                                          \
+    else if (g.b_once)                                                           \
+      ASYM_SMALL_M(mb, ns, true);                                                \
+    else                                                                         \
+      ASYM_SMALL_M(mb, ns, false);                                               \
+    break;
   switch (g.mb) {
-    // stages of 8 k-steps (A stage 16 / 32 KiB of LDS); 4 with 64 rows (32 KiB)
-    case 1:
-      hipLaunchKernelGGL((gemm_bf16_small_m<1, 8>), dim3((unsigned)grid), dim3(SK_THREADS), 0, s, p);
-      break;
-    case 2:
-      hipLaunchKernelGGL((gemm_bf16_small_m<2, 8>), dim3((unsigned)grid), dim3(SK_THREADS), 0, s, p);
-      break;
-    case 4:
-      hipLaunchKernelGGL((gemm_bf16_small_m<4, 4>), dim3((unsigned)grid), dim3(SK_THREADS), 0, s, p);
-      break;
+    ASYM_SMALL_M_CASE(1, 14, 7)
+    ASYM_SMALL_M_CASE(2, 12, 6)
+    ASYM_SMALL_M_CASE(4, 9, 5)
     default:
       return fail(ASYM_EINVAL, "small-M GEMM: row blocks must be 1, 2 or 4");
   }
+#undef ASYM_SMALL_M_CASE
+#undef ASYM_SMALL_M
   ASYM_HIP(hipGetLastError());
   if (p.ksplit > 1) {
     const long long threads = (long long)p.tiles_n * 16 * g.mb * 16;

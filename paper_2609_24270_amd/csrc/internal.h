@@ -116,6 +116,8 @@ struct SmallMLaunch {
   int row_tiles = 1;            // plain GEMM: row tiles of 16 mb rows
   int order = 0;                // plain GEMM: 0 aware, 1 column-major, 2 row-major
   int n_x = 8;                  // XCDs
+  int device_cus = 256;         // compute units of the device
+  bool b_once = false;          // B is loaded non-temporally: one workgroup per row of it, and more than a cache keeps
   long long grid = 0;           // workgroups
   const void* d_desc = nullptr; // grouped: device int4 per workgroup {row, rows, B row, column}
   int tile_cols = 64;           // columns per column tile: a multiple of 8 up to 64 (plain, unsplit)

@@ -294,3 +294,21 @@ def test_narrow_column_tiles(dev, M, N, K, width):
     cols = np.unique(np.concatenate([g.choice(N, min(N, 400), replace=False), np.arange(N - width, N)]))
     R, _ = oracle.gemm_bf16(bits(A), bits(B)[cols], "nk")
     assert_gemm_close(outs[0][:, cols], R, what=f"{M}x{N}x{K} in {width}-column tiles")
+
+
+# both ring depths (workgroups up to, and past, the 256 CUs), B on both sides of
+# the size from which rows read once bypass the caches (64 MiB), K shorter than
+# the ring, odd and even stage counts and a last stage of one 8-k chunk
+@pytest.mark.parametrize("M", [3, 32, 50, 130])
+@pytest.mark.parametrize("N,K", [(16392, 2056), (16384, 2040), (40000, 8), (17000, 328), (16000, 904)])
+def test_ring_depths_and_cache_policy(dev, M, N, K):
+    A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M + K, dist="int"))
+    C = torch.full((M, N + 4), 3.0, dtype=torch.bfloat16, device=dev)
+    Ad, Bd = A.to(dev), B.to(dev)
+    g = np.random.default_rng(M)
+    cols = np.unique(np.concatenate([g.choice(N, 300, replace=False), np.arange(64), np.arange(N - 80, N)]))
+    _, Co = oracle.gemm_bf16(bits(A), bits(B)[cols], "nk")
+    for m in MAPS:
+        asym.gemm(Ad, Bd, C[:, :N], mapping=m)
+        assert torch.all(C[:, N:] == 3.0)
+        assert np.array_equal(bits(C[:, :N])[:, cols], Co), m
