@@ -15,7 +15,10 @@
 //     quarter of the block's tokens, value rows are 16-byte loads, and the
 //     probabilities reach it through a per-wave LDS tile (V's layout puts the
 //     token index across rows, which an MFMA operand would need transposed);
-//   * the next block's K and V are in flight while a block is computed.
+//   * the next block's K and V are in flight while a block is computed, loaded
+//     non-temporally where they are more than the memory-side cache holds in
+//     part (what bounds a long cache is the rate of these loads: 16 requests,
+//     8 heads, 8000 tokens, 524 MB, 102 us, non-temporal 90, 5.8 TB/s).
 // Each task writes its unnormalised output, max and sum (fp32); a second
 // kernel merges the splits of each (request, head) in an order fixed by the
 // split count (several waves per row when there are many splits), so the
@@ -90,8 +93,8 @@ __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w <<
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
 // One task on one wave.  G: query heads per key/value head (1 .. 16);
-// PAGED: K and V through the page tables.
-template <int G, bool PAGED>
+// PAGED: K and V through the page tables; ONCE: K and V loaded non-temporally.
+template <int G, bool PAGED, bool ONCE>
 __device__ void attn_task(const AttnParams& p, int task, float* __restrict__ sp) {
   const int lane = threadIdx.x & 63;
   const int split = task % p.n_splits;
@@ -142,12 +145,13 @@ __device__ void attn_task(const AttnParams& p, int task, float* __restrict__ sp)
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
 
+  constexpr int kPolicy = ONCE ? 2 : 0;  // 2: the nt bit
   auto load_k = [&](int blk, bf16x8 (&kf)[4]) {
     const int tok = t0 + blk * 16 + lr;
     const uint32_t base = tok < t1 ? blk_off(blk, kpg) + (uint32_t)(lr * AD + lq * 8) * 2u : kAtOOB;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      kf[c] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, base, 64 * c, 0));
+      kf[c] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, base, 64 * c, kPolicy));
   };
   auto load_v = [&](int blk, v4u (&vf)[4]) {
     const uint32_t r0 = blk_off(blk, vpg);
@@ -155,7 +159,7 @@ __device__ void attn_task(const AttnParams& p, int task, float* __restrict__ sp)
     for (int i = 0; i < 4; ++i) {
       const int tok = t0 + blk * 16 + 4 * i + lq;
       vf[i] = __builtin_amdgcn_raw_buffer_load_b128(
-          rv, tok < t1 ? r0 + (uint32_t)((4 * i + lq) * AD + lr * 8) * 2u : kAtOOB, 0, 0);
+          rv, tok < t1 ? r0 + (uint32_t)((4 * i + lq) * AD + lr * 8) * 2u : kAtOOB, 0, kPolicy);
     }
   };
 
@@ -255,14 +259,14 @@ __device__ void attn_task(const AttnParams& p, int task, float* __restrict__ sp)
   }
 }
 
-template <int G, bool PAGED>
+template <int G, bool PAGED, bool ONCE>
 __global__ void __launch_bounds__(64 * AT_WAVES) attn_decode_split(AttnParams p) {
   __shared__ float sp_all[AT_WAVES][256 + 16];
   __shared__ int box[2];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (!p.quota_off) {
     const int task = blockIdx.x * AT_WAVES + wave;
-    if (task < p.tasks) attn_task<G, PAGED>(p, task, sp_all[wave]);
+    if (task < p.tasks) attn_task<G, PAGED, ONCE>(p, task, sp_all[wave]);
     return;
   }
   uint32_t xr;
@@ -308,7 +312,7 @@ __global__ void __launch_bounds__(64 * AT_WAVES) attn_decode_split(AttnParams p)
     const int base = box[0], end = box[1];
     __syncthreads();
     if (base < 0) break;
-    if (base + wave < end) attn_task<G, PAGED>(p, base + wave, sp_all[wave]);
+    if (base + wave < end) attn_task<G, PAGED, ONCE>(p, base + wave, sp_all[wave]);
   }
 }
 
@@ -359,12 +363,18 @@ int launch_attn_decode(const AttnLaunch& a, hipStream_t s) {
   const bool paged = a.k_page != nullptr;
   if (paged && (!a.v_page || a.pool_bytes == 0 || a.pool_bytes > (1u << 31) || a.split > 64 * kPageTokens))
     return fail(ASYM_EINVAL, "attention: a paged launch needs both tables, pools of at most 2 GiB, splits of <= 2048");
-#define ASYM_ATTN_CASE(g)                                                      \
-  case g:                                                                      \
-    if (paged)                                                                 \
-      hipLaunchKernelGGL((attn_decode_split<g, true>), grid, block, 0, s, p);  \
-    else                                                                       \
-      hipLaunchKernelGGL((attn_decode_split<g, false>), grid, block, 0, s, p); \
+#define ASYM_ATTN_SPLIT(g, paged, once) \
+  hipLaunchKernelGGL((attn_decode_split<g, paged, once>), grid, block, 0, s, p)
+#define ASYM_ATTN_CASE(g)                \
+  case g:                                \
+    if (paged && a.once)                 \
+      ASYM_ATTN_SPLIT(g, true, true);    \
+    else if (paged)                      \
+      ASYM_ATTN_SPLIT(g, true, false);   \
+    else if (a.once)                     \
+      ASYM_ATTN_SPLIT(g, false, true);   \
+    else                                 \
+      ASYM_ATTN_SPLIT(g, false, false);  \
     break;
   switch (G) {
     ASYM_ATTN_CASE(1)
@@ -375,6 +385,7 @@ int launch_attn_decode(const AttnLaunch& a, hipStream_t s) {
     default: return fail(ASYM_EUNSUPPORTED, "attention: query heads per key/value head must be 1, 2, 4, 8 or 16");
   }
 #undef ASYM_ATTN_CASE
+#undef ASYM_ATTN_SPLIT
   ASYM_HIP(hipGetLastError());
   const int rows = a.B * a.Hq;
   const int wpr = merge_waves_per_row(a.n_splits), rows_per_wg = kMergeWaves / wpr;

@@ -144,6 +144,7 @@ struct AttnLaunch {
   const int* k_page = nullptr;  // paged form: device tables [B][Hkv][ceil(S / 32)]; null = dense K, V
   const int* v_page = nullptr;
   uint32_t pool_bytes = 0;      // paged form: bytes of each pool (<= 2^31)
+  bool once = false;            // K and V are loaded non-temporally
 };
 int launch_attn_decode(const AttnLaunch& a, hipStream_t s);
 int attn_tasks_per_workgroup();

@@ -152,3 +152,20 @@ def test_paged_rejections(dev):
     assert lib.asym_attn_decode_paged_bf16(*args(tp, tp, 0)) == asym.EINVAL
     assert lib.asym_attn_decode_paged_bf16(*args(tp, tp, (1 << 18) + 1)) == asym.EINVAL
     assert lib.asym_attn_decode_paged_bf16(*args(ctypes.c_void_p(t.data_ptr() + 2), tp, 4)) == asym.EINVAL
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,S", [(8, 8, 34, 1009), (16, 8, 2, 16417), (32, 4, 20, 3300), (32, 2, 130, 1040)])
+def test_cache_policy_changes_no_bits(dev, Hq, Hkv, B, S):
+    """From 128 MiB of keys and values on they are loaded non-temporally; the
+    batch as one such call equals its halves, dense and paged, bit for bit."""
+    assert 2 * B * Hkv * S * 256 >= 128 << 20 > 2 * (B // 2) * Hkv * S * 256
+    g = torch.Generator(device=dev).manual_seed(S)
+    q = torch.randn(B, Hq, 128, device=dev, generator=g).bfloat16()
+    k, v = (torch.randn(B, Hkv, S, 128, device=dev, generator=g).bfloat16() for _ in range(2))
+    pph = -(-S // 32)
+    t = torch.randperm(B * Hkv * pph, device=dev, generator=g).to(torch.int32).view(B, Hkv, pph)
+    kp, vp = (workloads.page_pool(x, t, t.numel()) for x in (k, v))
+    h = B // 2
+    halves = torch.cat([asym.attn_decode(q[i:i + h], k[i:i + h], v[i:i + h], split_tokens=512) for i in (0, h)])
+    assert torch.equal(asym.attn_decode(q, k, v, split_tokens=512), halves)
+    assert torch.equal(asym.attn_decode_paged(q, kp, vp, t, t, S, split_tokens=512), halves)
