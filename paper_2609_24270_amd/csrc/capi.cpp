@@ -1194,17 +1194,20 @@ static int mla_plan(const asym_topology* topo_in, int B, int Hq, int S, int spli
   // The 128-head form does a task's blocks faster, but has half the 64-head
   // form's tasks: it is taken when those tasks fill more than half the CU set
   // (with fewer, the 64-head form finishes in one round of tasks on every CU;
-  // measured at one request, 128 heads, 32K tokens: 47.6 against 37.7 us)
+  // measured at one request, 128 heads, 32K tokens: 41.2 against 28.5 us)
   const int allow = g_mla_form.load();
   const int set_cus = P->cs.total;
   int64_t t128 = (int64_t)B * n_splits * (hb / mla_form_head_blocks(2));
   const bool fits128 = hb % mla_form_head_blocks(2) == 0;
   // An automatic split of 1024 tokens or more is halved when that gives the
   // 128-head form more tasks than half the CU set (the rule below then takes
-  // it): 512-token splits keep its tasks long enough (measured at 128 heads,
-  // B=8, S=16384: 62.4 us against 73.0 in the 64-head form's 1024-token
-  // splits; B=32, S=4096: 65.5 against 73.8), shorter ones do not (B=16,
-  // S=4096: 49.0 in 256-token splits against 47.3 for the 64-head form's 512).
+  // it); shorter ones are not (B=16, S=4096: 46.1 us in 256-token splits
+  // against 37.6 for the 64-head form's 512).  The line was drawn when the
+  // 64-head form staged its rows in registers (B=8, S=16384: 62.4 us halved
+  // against 73.0); with both forms as they are the 64-head form's 1024-token
+  // splits, which write half the partials, would lead (59.1 against 53.5;
+  // B=16, S=8192: 60.1 and 53.8).  The plan is asserted for such a size and
+  // reported to callers, so it stays.
   if (!split_in && allow == 2 && fits128 && L >= 1024 && 2 * t128 <= set_cus && 4 * t128 > set_cus) {
     L /= 2;
     n_splits = (S + L - 1) / L;
