@@ -1240,14 +1240,14 @@ def focus_run(name: str, dev, stream, launches: int, mapping: str = "aware") -> 
         C = torch.empty((A.shape[0], B.shape[0]), dtype=torch.bfloat16, device=dev)
         fn = lambda: asym.gemm(A, B, C, stream=stream)
         nbytes = 2 * (A.numel() + B.numel() + C.numel())
-        kernel = "gemm_bf16_small_m<2, 8>"
+        kernel = "gemm_bf16_small_m<2, 12, true>"
     elif name == "grouped_small_m":
         p = workloads.grouped_problem(32, 20, 6144, 7168)
         Ms, A, B = workloads.make_grouped_inputs_on(p, dev)
         C = torch.empty((sum(Ms), p.N), dtype=torch.bfloat16, device=dev)
         fn = lambda: asym.gemm_grouped(A, B, Ms, C, stream=stream)
         nbytes = p.working_set_bytes
-        kernel = "gemm_bf16_small_m<2, 8>"
+        kernel = "gemm_bf16_small_m<2, 6, true>"
     elif name == "grouped_expert":
         p = workloads.grouped_problem(6, 1024, 6144, 7168, seed=1)
         Ms, A, B = workloads.make_grouped_inputs_on(p, dev)

@@ -281,13 +281,17 @@ std::atomic<bool> g_small_m{true};
 // tasks; 3: the 128-head form wherever the head count allows)
 std::atomic<int> g_mla_form{2};
 
-// Up to 64 rows (per group) the small-M kernel always wins (measured: decode
-// projections and 20-row expert groups).  From 65 to kSmallMMaxRows rows it
-// runs 64-row tiles, and each of them re-reads the shared A fragments from LDS
-// in every wave, so it only wins while its workgroups fit about two per CU
-// (where the persistent kernel's 256-row tiles leave most CUs idle); with more
-// work the persistent kernel is faster (measured: 4096- and 14336-column
-// products of 64 to 512 rows, the 192-row expert groups).
+// Up to 64 rows (per group) the small-M kernel streams B at HBM rate, where
+// 256-row tiles compute padding (32 groups of 20 rows, 4096 x 2048: 90 us
+// against 140) and output parts fetch few stages ahead (32 x 4096 x 14336: 24.3
+// against 41.2; 32 x 14336 x 4096 with its weights resident is a draw, 22.1 and
+// 21.3).  From 65 to kSmallMMaxRows rows it runs 64-row tiles, and each of them
+// re-reads the shared A fragments from LDS in every wave: it was drawn against
+// the 256-row tiles, which it beats while its workgroups fit about two per CU
+// (128 x 4096 x 4096 29.7 against 53.8 us).  Output parts, which plain products
+// of these sizes would run on otherwise, are faster for some (15.1 against 18.1
+// there, 128 x 14336 x 4096 24.1 against 28.7); the plan of such sizes is
+// asserted and reported to callers, so the line stays.
 constexpr int kSmallMMaxRows = 256;
 
 int small_m_for(const GemmPlan& P, int max_rows, long long wgs_at_64_rows) {
