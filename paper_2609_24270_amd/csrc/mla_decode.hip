@@ -375,8 +375,13 @@ __device__ __forceinline__ i32x4 ml_rsrc_words(const void* base, uint32_t bytes)
 // LDS: lane L's bytes land at lds + 16 L.  The compiler does not see these
 // loads; their completion is waited for explicitly (ml_vmwait) before the
 // barrier that publishes the tile.
+template <bool NT>  // non-temporal
 __device__ __forceinline__ void ml_dma16(uint32_t lds, i32x4 rs, uint32_t voff, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 : : "s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                : : "s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
 }
 template <int N>
@@ -402,7 +407,7 @@ __device__ __forceinline__ void ml_pin(f32x4 (&o)[NH][MV / 16]) {
     for (int j = 0; j < MV / 16; ++j) asm volatile("" : "+a"(o[h][j]));
 }
 
-template <int NH>
+template <int NH, bool ONCE>
 __device__ void mla_wg_task(const MlaParams& p, int b, int split, int hg, unsigned char* __restrict__ tiles) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -445,7 +450,7 @@ __device__ void mla_wg_task(const MlaParams& p, int b, int split, int hg, unsign
     i32x4 rs = rk;
     rs[2] = __builtin_amdgcn_readfirstlane(blk < nblk ? rk[2] : 0);
     const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane((t0 + blk * MT2) * (MD * 2) + g * 128);
-    ml_dma16(lds_base + tile_at(blk) + (uint32_t)(g * T2_GROUP_BYTES + wave * 1024), rs, voff, so);
+    ml_dma16<ONCE>(lds_base + tile_at(blk) + (uint32_t)(g * T2_GROUP_BYTES + wave * 1024), rs, voff, so);
   };
   // key fragment of step c, rows 16 half + lr: chunk 4 (c & 1) + lq of piece c / 2
   const uint32_t kb0 = (uint32_t)(lr * 128 + (lq ^ ((lr >> 1) & 7)) * 16);
@@ -673,15 +678,17 @@ __global__ void __launch_bounds__(64 * MW) mla_decode_split(MlaParams p) {
 // with the group fastest (aware) or group major (oblivious).  Oblivious: task
 // i on workgroup i.  Aware: claims of one task, own share first, then the
 // others, as in the wave form.
-// FORM: head blocks per wave.
-template <int FORM>
+// KIND 1, 2: that many head blocks per wave; 3, 4: the same with the rows loaded
+// non-temporally.
+template <int KIND>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) mla_decode_split_wg(MlaParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char tiles[T2_TILES * T2_BYTES];
   __shared__ int box[1];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const bool aware = p.quota_off != nullptr;
-  const int groups = p.hblocks / (MG * FORM);
+  constexpr int NH = KIND > 2 ? KIND - 2 : KIND;
+  const int groups = p.hblocks / (MG * NH);
   int own = 0;
   if (aware) {
     uint32_t xr;
@@ -737,7 +744,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
       split = r % p.n_splits;
       b = r / p.n_splits;
     }
-    mla_wg_task<FORM>(p, b, split, hg, tiles);
+    mla_wg_task<NH, (KIND > 2)>(p, b, split, hg, tiles);
   }
 }
 
@@ -778,11 +785,19 @@ int launch_mla_decode(const MlaLaunch& a, hipStream_t s) {
   p.scale = a.scale;
   if (a.d_quota_off && (!a.d_claim || a.n_x > 64)) return fail(ASYM_EINVAL, "mla: aware launch without claim counters");
   if (a.grid < 1) return fail(ASYM_EINVAL, "mla: empty grid");
-  if (a.form == 2)
-    hipLaunchKernelGGL(mla_decode_split_wg<2>, dim3((unsigned)a.grid), dim3(256), 0, s, p);
-  else if (a.form == 1)
-    hipLaunchKernelGGL(mla_decode_split_wg<1>, dim3((unsigned)a.grid), dim3(256), 0, s, p);
-  else
+  // Where one workgroup reads a row for all its heads, rows that exceed the
+  // memory-side cache (256 MiB) are loaded non-temporally; smaller caches may
+  // still be resident, and several groups of heads share a row's second read.
+  // Measured, caches of four calls in turn, us, ordinary loads first: 128 heads,
+  // 151 MB 63.3 and 63.5 (resident 59.1 and 63.5), 604 MB 196 and 187, 2.4 GB
+  // 607 and 594; 64 heads, 604 MB 149 and 138.  The wave form's loads lose
+  // everywhere (16 heads, 604 MB 123 and 126).
+  const bool once = p.hblocks == per_task && (int64_t)a.B * a.S * MD * 2 >= (256ll << 20);
+  if (a.form != 0) {
+    auto split_wg = a.form == 2 ? (once ? mla_decode_split_wg<4> : mla_decode_split_wg<2>)
+                                : (once ? mla_decode_split_wg<3> : mla_decode_split_wg<1>);
+    hipLaunchKernelGGL(split_wg, dim3((unsigned)a.grid), dim3(256), 0, s, p);
+  } else
     hipLaunchKernelGGL(mla_decode_split, dim3((unsigned)a.grid), dim3(64 * MW), 0, s, p);
   ASYM_HIP(hipGetLastError());
   const int rows = a.B * a.Hq;

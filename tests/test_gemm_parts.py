@@ -73,7 +73,7 @@ def test_operand_rule_sees_a_planted_write():
     assert not operand_violations(bad.replace("\t;;#ASMSTART", "\ts_nop 7\n\t;;#ASMSTART", 1), "k")
 
 
-@pytest.mark.parametrize("form", [1, 2])
+@pytest.mark.parametrize("form", [1, 2, 3, 4])  # 3, 4: non-temporal rows
 def test_latent_attention_workgroup_forms_hazards(tmp_path, form):
     asm = _asm_vgpr_form("mla_decode.hip", tmp_path)
     kernel = f"_ZN4asym12_GLOBAL__N_119mla_decode_split_wgILi{form}EEEvNS0_9MlaParamsE"

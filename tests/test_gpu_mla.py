@@ -255,3 +255,17 @@ def test_mla_workgroup_form(dev, topo, B, Hq, S, split):
     heads = None if B * Hq * S <= 200_000 else sorted(set([0, Hq - 1, Hq // 2, 17 % Hq]))
     check(q, kv, got, lse_g, p.scale, f"mla workgroup form B{B} H{Hq} S{S}", heads=heads)
     check(q, kv, wave, lse_w, p.scale, f"mla wave form B{B} H{Hq} S{S}", heads=heads)
+
+
+@pytest.mark.parametrize("Hq", [64, 128])
+def test_cache_policy_changes_no_bits(dev, Hq):
+    """Rows of more than 256 MiB are loaded non-temporally by the workgroup
+    forms; the batch as one such call equals its halves bit for bit."""
+    B, S = 58, 4099
+    assert B * S * 1152 >= 256 << 20 > B // 2 * S * 1152
+    g = torch.Generator(device=dev).manual_seed(Hq)
+    q = torch.randn(B, Hq, 576, device=dev, generator=g).bfloat16()
+    kv = torch.randn(B, S, 576, device=dev, generator=g).bfloat16()
+    h = B // 2
+    halves = [asym.mla_decode(q[i:i + h], kv[i:i + h], split_tokens=512) for i in (0, h)]
+    assert torch.equal(asym.mla_decode(q, kv, split_tokens=512), torch.cat(halves))
