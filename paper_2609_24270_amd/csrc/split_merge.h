@@ -61,7 +61,7 @@ __device__ __forceinline__ void merge_split_rows(const float* __restrict__ part_
   static_assert(DPL == 1 || DPL == 2 || DPL == 4 || DPL == 8, "1 to 8 values per lane");
   __shared__ float red[kMergeWaves][DC];
   __shared__ float red_l[kMergeWaves];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int rows_per_wg = kMergeWaves / wpr;
   const int row = blockIdx.x * rows_per_wg + wave / wpr;
   const int c0 = (int)blockIdx.y * DC + DPL * lane;  // this lane's first column
@@ -74,25 +74,33 @@ __device__ __forceinline__ void merge_split_rows(const float* __restrict__ part_
   // The wave's first eight splits go out before anything else is waited for:
   // a merge is a few microseconds of memory latency, and the row's max, which
   // the weights need, would otherwise be a round trip of its own before them.
-  // Splits past the last load the last one again and are not added.
+  // Of these, splits past the last are not loaded: short calls have rows of one
+  // split (16 requests x 64 tokens, 10.4 us a call with it loaded eight times
+  // over, 9.6 once).
   typedef typename MergeVec<DPL>::type vrow;
   vrow x[8];
   float2 q[8];
-  auto load = [&](int s0) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int s = min(s0 + u * wpr, n_splits - 1);
-      x[u] = *reinterpret_cast<const vrow*>(po + (size_t)s * D);
-      q[u] = *reinterpret_cast<const float2*>(ml + 2 * s);
-    }
+  int zero = 0;  // (in a vector register: scalar loads of q would be waited for one by one)
+  asm volatile("" : "+v"(zero));
+  auto load = [&](int u, int s) {
+    x[u] = *reinterpret_cast<const vrow*>(po + (size_t)s * D);
+    q[u] = *reinterpret_cast<const float2*>(ml + (2 * s + zero));
   };
-  load(sub);
-  // the row's max over every split, 256 at a time (the last one again past it)
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    if (sub + u * wpr < n_splits)
+      load(u, sub + u * wpr);
+    else
+      asm volatile("" : "=v"(x[u]), "=v"(q[u]));  // (defined, whatever it holds: the batch's asm below names it)
+  }
+  // the row's max over every split, up to 256 at a time (the last one again
+  // in the lanes past it)
   float M = -INFINITY;
-  for (int s = lane; s < n_splits; s += 256) {
+  for (int s0 = 0; s0 < n_splits; s0 += 256) {
     float m[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) m[u] = ml[2 * min(s + 64 * u, n_splits - 1)];
+    for (int u = 0; u < 4; ++u)
+      m[u] = s0 + 64 * u < n_splits ? ml[2 * min(s0 + 64 * u + lane, n_splits - 1)] : -INFINITY;
     M = fmaxf(M, fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])));
   }
 #pragma unroll
@@ -101,7 +109,10 @@ __device__ __forceinline__ void merge_split_rows(const float* __restrict__ part_
   vrow acc = {};
   float L = 0.f;
   for (int s0 = sub; s0 < n_splits; s0 += 8 * wpr) {
-    if (s0 != sub) load(s0);
+    if (s0 != sub) {  // (past the first eight: the last one again past it, not added)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) load(u, min(s0 + u * wpr, n_splits - 1));
+    }
     // one empty asm that takes the whole batch: every load is issued before
     // the first of them is waited for (the compiler would otherwise place
     // each load next to its use, one memory latency per split)

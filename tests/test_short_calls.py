@@ -1,0 +1,26 @@
+"""What a short call pays for: work that only longer calls need must stand
+behind a branch (CPU: the compiled kernels; GPU: results at those sizes)."""
+import re
+
+import pytest
+
+from tests.test_kernel_fragments import blocks_of
+from tests.test_kernel_structure import asm_of
+
+
+def _kernels(asm, name):
+    found = sorted(set(re.findall(rf"^(_ZN4asym\S*{name}\S*):", asm, re.M)))
+    assert found, name
+    return found
+
+
+@pytest.mark.parametrize("src,name", [("attn_decode.hip", "attn_decode_merge"), ("mla_decode.hip", "mla_decode_merge")])
+def test_merge_loads_only_the_splits_there_are(tmp_path, src, name):
+    """A wave's first eight splits are loaded one by one, each behind a branch,
+    so a row of one split costs one split's loads; whole batches stand in the
+    loop over further splits alone."""
+    asm = asm_of(src, tmp_path)
+    for k in _kernels(asm, name):
+        loads = [sum(i.startswith("global_load") for i, _ in b["insts"]) for b in blocks_of(asm, k)]
+        assert sum(n > 4 for n in loads) <= 1, (k, loads)
+        assert sum(n in (2, 3) for n in loads) >= 8, (k, loads)
