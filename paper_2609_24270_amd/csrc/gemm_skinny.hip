@@ -100,6 +100,22 @@ __device__ __forceinline__ void sk_dma(uint32_t lds, i32x4 rs, uint32_t voff, ui
                  : : "s"(lds), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
 }
 
+// The last R stages of a ring, all of whose loads (LPS a wave and stage) are
+// issued.  Stage J's fragments are in `cur`, stages up to END have been
+// published, and `slot` is that of stage J + 1.
+template <int R, int J, int LPS, int END = 0, typename Frags, typename Read, typename Mfmas, typename After>
+__device__ __forceinline__ void sk_tail(Frags& cur, Frags& nxt, uint32_t slot, Read& read, Mfmas& mfmas, After& after) {
+  if constexpr (J + 1 < R) {
+    constexpr int NEXT = J == END ? J + (R - J) / 2 : END;
+    if constexpr (NEXT != END) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((R - 1 - NEXT) * LPS) : "memory");
+    read(nxt, slot);
+    mfmas(cur);
+    sk_tail<R, J + 1, LPS, NEXT>(nxt, cur, after(slot), read, mfmas, after);
+  } else {
+    mfmas(cur);
+  }
+}
+
 // MB: 16-row blocks of the row tile (1, 2 or 4); NS: ring slots; ONCE: no other
 // workgroup reads this one's B rows, and they are loaded non-temporally.
 template <int MB, int NS, bool ONCE>
@@ -215,6 +231,14 @@ __global__ void __launch_bounds__(SK_THREADS) gemm_bf16_small_m(SkinnyParams p) 
   f32x4 acc[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mfmas = [&](const Frags& f) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[h], f.a[h][i], acc[i], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
   // Stage t, its fragments in `cur`: publish stage t + 1 (this wave's loads of
   // it have landed; loads complete in order), read it into `nxt`, reload the
   // slot of stage t - 1 (`sl`: its reads were waited for before its MFMAs, which
@@ -223,32 +247,56 @@ __global__ void __launch_bounds__(SK_THREADS) gemm_bf16_small_m(SkinnyParams p) 
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 3) * LPS) : "memory");
     read(nxt, sn);
     load(t + NS - 1, sl);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[h], cur.a[h][i], acc[i], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
+    mfmas(cur);
   };
+  // Stages past the last are not loaded: loads that only fill zeros take the
+  // address unit as long as any others, and a K of a few stages paid for a ring of
+  // them and for a barrier a stage.  The last R stages run without loads and with
+  // four barriers, a shorter K with one.  16 x 4096 x 512 3.46 us, zero-filled
+  // 4.46 (B into registers, before there was a ring, 3.55); 16 x 6144 x 4096, K in
+  // 8 ranges, 14.9, 17.5 (16.2); 32 x 14336 x 4096 22.5, 24.1 (33.3).
   constexpr uint32_t RING = NS * SLOT;
+  constexpr int R = NS - 1;  // stages in flight
   auto after = [](uint32_t slot) { return slot + SLOT == RING ? 0u : slot + SLOT; };
   Frags f0, f1;
+  if (KT >= R) {
 #pragma unroll
-  for (int t = 0; t < NS - 1; ++t) load(t, t * SLOT);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LPS) : "memory");
-  read(f0, 0);
-  uint32_t sl = RING - SLOT, sc = 0, sn = SLOT;  // slots of stages t - 1, t, t + 1
-  int t = 0;
-  for (; t + 1 < KT; t += 2) {
-    stage(t, f0, f1, sn, sl);
-    const uint32_t s2 = after(sn);
-    stage(t + 1, f1, f0, s2, sc);
-    sl = sn;
-    sc = s2;
-    sn = after(s2);
+    for (int t = 0; t < R; ++t) load(t, t * SLOT);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((R - 1) * LPS) : "memory");
+    read(f0, 0);
+    uint32_t sl = RING - SLOT, sc = 0, sn = SLOT;  // slots of stages t - 1, t, t + 1
+    int t = 0;
+    for (; t + R + 1 < KT; t += 2) {
+      stage(t, f0, f1, sn, sl);
+      const uint32_t s2 = after(sn);
+      stage(t + 1, f1, f0, s2, sc);
+      sl = sn;
+      sc = s2;
+      sn = after(s2);
+    }
+    if (t + R < KT) {
+      stage(t, f0, f1, sn, sl);
+      f0 = f1;
+      sn = after(sn);
+    }
+    // The last R stages, all loaded, the first one's fragments in f0: a wait and
+    // a barrier for half of what is in flight, then half of the rest, ...
+    sk_tail<R, 0, LPS>(f0, f1, sn, read, mfmas, after);
+  } else {
+    for (int t = 0; t < KT; ++t) load(t, t * SLOT);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    read(f0, 0);  // (reads past the last stage are not used)
+    int t = 0;
+    uint32_t sn = SLOT;
+    for (; t + 1 < KT; t += 2) {
+      read(f1, sn);
+      mfmas(f0);
+      read(f0, sn + SLOT);
+      mfmas(f1);
+      sn += 2 * SLOT;
+    }
+    if (t < KT) mfmas(f0);
   }
-  if (t < KT) stage(t, f0, f1, sn, sl);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zero fills past the end land before the LDS is given back
 
   // in a 16x16 block the lane with row r = lane % 16 holds columns 4c..4c+3,
   // c = lane / 16; rows past the tile fall outside the resource

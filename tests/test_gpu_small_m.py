@@ -312,3 +312,21 @@ def test_ring_depths_and_cache_policy(dev, M, N, K):
         asym.gemm(Ad, Bd, C[:, :N], mapping=m)
         assert torch.all(C[:, N:] == 3.0)
         assert np.array_equal(bits(C[:, :N])[:, cols], Co), m
+
+
+@pytest.mark.parametrize("M", [3, 20, 50])  # 16, 32 and 64 rows a tile: rings of 14 and 7, 12 and 6, 9 and 5 slots
+@pytest.mark.parametrize("N", [16384, 20000])  # up to one workgroup per CU: the deep ring; more: the other
+def test_every_ring_fill(dev, M, N):
+    """K of 1 to 20 stages of 64, the last one ragged: shorter than the ring, as
+    long as it, and past it by odd and even numbers of stages."""
+    g = np.random.default_rng(M)
+    cols = np.unique(np.concatenate([g.choice(N, 60, replace=False), np.arange(40), np.arange(N - 40, N)]))
+    for KT in range(1, 21):
+        K = 64 * KT - 8 * (KT % 8)
+        A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=K, dist="int"))
+        Ad, Bd = A.to(dev), B.to(dev)
+        plan = asym.gemm_plan(Ad, Bd, torch.empty(M, N, dtype=torch.bfloat16, device=dev))
+        cus = torch.cuda.get_device_properties(dev).multi_processor_count
+        assert plan["small_m"] == 1 and plan["k_splits"] == 1 and (plan["grid"] <= cus) == (N == 16384)
+        _, Co = oracle.gemm_bf16(bits(A), bits(B)[cols], "nk")
+        assert np.array_equal(bits(asym.gemm(Ad, Bd))[:, cols], Co), K

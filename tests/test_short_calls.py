@@ -24,3 +24,18 @@ def test_merge_loads_only_the_splits_there_are(tmp_path, src, name):
         loads = [sum(i.startswith("global_load") for i, _ in b["insts"]) for b in blocks_of(asm, k)]
         assert sum(n > 4 for n in loads) <= 1, (k, loads)
         assert sum(n in (2, 3) for n in loads) >= 8, (k, loads)
+
+
+def test_small_m_ring_loads_only_the_stages_there_are(tmp_path):
+    """The ring is filled in one run only where K fills it; a shorter K loads its
+    stages in a loop, and the last stages of any K load nothing."""
+    asm = asm_of("gemm_skinny.hip", tmp_path)
+    for k in _kernels(asm, "gemm_bf16_small_mI"):
+        lps = 4 if "ILi4E" in k else 3
+        loads, mfmas = [], []
+        for b in blocks_of(asm, k):
+            loads.append(sum(bool(re.match(r"buffer_load.*\blds$", i)) for i, _ in b["insts"]))
+            mfmas.append(sum(i.startswith("v_mfma") for i, _ in b["insts"]))
+        assert sum(n > 2 * lps for n in loads) == 1, (k, loads)
+        assert any(n == lps and not m for n, m in zip(loads, mfmas)), (k, loads)
+        assert loads[mfmas.index(max(mfmas))] == 0, (k, loads, mfmas)
