@@ -122,7 +122,9 @@ __device__ void attn_task(const AttnParams& p, int task, float* __restrict__ sp)
       vpg = p.v_page[e];
     }
   }
-  // byte offset of block blk's first row in its buffer
+  // byte offset of block blk's first row in its buffer.  Called by all lanes
+  // only: a lane that is off may hold the page that is asked for, and a register
+  // that the compiler moves or reloads while it is off lacks that lane's value.
   auto blk_off = [&](int blk, int pg) -> uint32_t {
     const int bt = t0 + blk * 16;
     if constexpr (PAGED)
@@ -148,7 +150,8 @@ __device__ void attn_task(const AttnParams& p, int task, float* __restrict__ sp)
   constexpr int kPolicy = ONCE ? 2 : 0;  // 2: the nt bit
   auto load_k = [&](int blk, bf16x8 (&kf)[4]) {
     const int tok = t0 + blk * 16 + lr;
-    const uint32_t base = tok < t1 ? blk_off(blk, kpg) + (uint32_t)(lr * AD + lq * 8) * 2u : kAtOOB;
+    const uint32_t r0 = blk_off(blk, kpg);
+    const uint32_t base = tok < t1 ? r0 + (uint32_t)(lr * AD + lq * 8) * 2u : kAtOOB;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
       kf[c] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, base, 64 * c, kPolicy));

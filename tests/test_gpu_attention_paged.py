@@ -169,3 +169,25 @@ def test_cache_policy_changes_no_bits(dev, Hq, Hkv, B, S):
     halves = torch.cat([asym.attn_decode(q[i:i + h], k[i:i + h], v[i:i + h], split_tokens=512) for i in (0, h)])
     assert torch.equal(asym.attn_decode(q, k, v, split_tokens=512), halves)
     assert torch.equal(asym.attn_decode_paged(q, kp, vp, t, t, S, split_tokens=512), halves)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (16, 4), (32, 4), (32, 2)])
+def test_ragged_last_block_on_a_later_page(dev, Hq, Hkv):
+    """A split's last block of fewer than 16 tokens that lies on its second page
+    or a later one: the lanes past its tokens hold the page number it needs.
+    Bitwise the dense call, and the oracle's values."""
+    B = 2
+    for S in (17, 33, 39, 49, 65, 100, 545, 561, 2001, 2609):
+        g = torch.Generator(device=dev).manual_seed(S)
+        q = torch.randn(B, Hq, 128, device=dev, generator=g).bfloat16()
+        k, v = (torch.randn(B, Hkv, S, 128, device=dev, generator=g).bfloat16() for _ in range(2))
+        pph = -(-S // 32)
+        tk, tv = (torch.randperm(B * Hkv * pph, device=dev, generator=g).to(torch.int32).view(B, Hkv, pph)
+                  for _ in range(2))
+        kp, vp = workloads.page_pool(k, tk, tk.numel()), workloads.page_pool(v, tv, tv.numel())
+        dense = asym.attn_decode(q, k, v, split_tokens=512)
+        assert torch.equal(asym.attn_decode_paged(q, kp, vp, tk, tv, S, split_tokens=512), dense), S
+        w = torch.softmax(q.cpu().float().view(B, Hkv, -1, 128) @ k.cpu().float().transpose(2, 3) / 128 ** 0.5, -1)
+        ref = (w @ v.cpu().float()).reshape(B, Hq, 128)
+        # bf16 probabilities and outputs: 2^-9 each, on values of the rows' size
+        assert ((dense.cpu().float() - ref).norm() / ref.norm()).item() < 2 ** -8, S

@@ -15,6 +15,8 @@ import subprocess
 
 import pytest
 
+from tests.test_kernel_fragments import blocks_of, successors
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2609_24270_amd", "csrc")
 
@@ -134,3 +136,40 @@ def test_gemm_tile_claim_is_published_in_its_own_loop(tmp):
     assert n >= 1
     text = "\n".join(body)
     assert not re.search(r"\bs_(store|atomic|buffer_store|dcache_wb|scratch_store)", text)
+
+
+def test_page_numbers_are_read_by_all_lanes(tmp_path):
+    """A paged call's lanes hold the split's page numbers, one each, and v_readlane
+    fetches the one a block needs, so the register must hold every lane's: no such
+    read stands where lanes are off, where the compiler may have moved the value
+    for the active lanes alone."""
+    asm = asm_of("attn_decode.hip", tmp_path)
+    kernels = re.findall(r"^(_ZN4asym\S*attn_decode_splitILi\d+ELb1\S*):", asm, re.M)
+    assert len(kernels) == 10
+    for k in kernels:
+        blocks = blocks_of(asm, k)
+        succ = successors(blocks)
+        off_at = [False] * len(blocks)  # lanes may be off where the block begins
+
+        def walk(b, off, seen=None):
+            for i, _ in blocks[b]["insts"]:
+                if re.match(r"s_(and|xor|andn2|or)\w*_saveexec_b64 |s_(and|xor|andn2)_b64 exec,", i):
+                    off = True
+                elif re.match(r"s_or_b64 exec, exec,|s_mov_b64 exec, -1", i):
+                    off = False
+                elif seen is not None and i.startswith("v_readlane_b32"):
+                    seen.append((off, i))
+            return off
+
+        todo = list(range(len(blocks)))
+        while todo:
+            b = todo.pop()
+            if walk(b, off_at[b]):
+                for n in succ[b]:
+                    if not off_at[n]:
+                        off_at[n] = True
+                        todo.append(n)
+        seen = []
+        for b in range(len(blocks)):
+            walk(b, off_at[b], seen)
+        assert len(seen) >= 4 and not any(off for off, _ in seen), (k, seen)
