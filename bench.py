@@ -1268,7 +1268,7 @@ def focus_run(name: str, dev, stream, launches: int, mapping: str = "aware") -> 
         o = torch.empty_like(q)
         fn = lambda: asym.attn_decode(q, k, v, o, stream=stream)
         nbytes = p.kv_bytes + 2 * 2 * q.numel()
-        kernel = "attn_decode_split<4, false, true> + attn_decode_merge"
+        kernel = "attn_decode_split<4, false, false> + attn_decode_merge"
     elif name in ("mla", "mla_long"):
         p = workloads.mla_problem(64, 128, 8192 if name == "mla" else 32768)
         q, kv = workloads.make_mla_inputs_on(p, dev)

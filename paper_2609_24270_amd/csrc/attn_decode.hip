@@ -16,9 +16,9 @@
 //     probabilities reach it through a per-wave LDS tile (V's layout puts the
 //     token index across rows, which an MFMA operand would need transposed);
 //   * the next block's K and V are in flight while a block is computed, loaded
-//     non-temporally where they are more than the memory-side cache holds in
-//     part (what bounds a long cache is the rate of these loads: 16 requests,
-//     8 heads, 8000 tokens, 524 MB, 102 us, non-temporal 90, 5.8 TB/s).
+//     non-temporally where they are more than the caches keep (what bounds a
+//     long cache is the rate of these loads: 16 requests, 8 heads, 8000 tokens,
+//     524 MB, 102 us, non-temporal 90, 5.8 TB/s).
 // Each task writes its unnormalised output, max and sum (fp32); a second
 // kernel merges the splits of each (request, head) in an order fixed by the
 // split count (several waves per row when there are many splits), so the

@@ -17,6 +17,7 @@
 #include <tuple>
 
 #include "internal.h"
+#include "read_policy.h"
 
 struct asym_topology;
 
@@ -1124,11 +1125,7 @@ int attn_decode(const asym_topology* topo_in, int B, int Hq, int Hkv, int S, int
   a.split = P.split; a.n_splits = P.n_splits;
   a.n_x = n_x; a.grid = P.grid;
   a.scale = scale;
-  // Every K and V byte is read once.  From half the memory-side cache (256 MiB)
-  // on they are loaded non-temporally: measured, caches of several calls in
-  // turn, us, ordinary loads first: 66 MB 18.7 and 20.4 (paged 20.8 and 22.7),
-  // 134 MB 33.1 and 31.1, 268 MB 54.1 and 49.6, 524 MB 102 and 90.
-  a.once = 2ll * B * Hkv * S * D * 2 >= (128ll << 20);
+  a.once = attn_streams_kv(2ll * B * Hkv * S * D * 2);
   if (paged) {
     a.k_page = k_pages;
     a.v_page = v_pages;

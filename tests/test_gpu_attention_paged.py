@@ -154,11 +154,11 @@ def test_paged_rejections(dev):
     assert lib.asym_attn_decode_paged_bf16(*args(ctypes.c_void_p(t.data_ptr() + 2), tp, 4)) == asym.EINVAL
 
 
-@pytest.mark.parametrize("Hq,Hkv,B,S", [(8, 8, 34, 1009), (16, 8, 2, 16417), (32, 4, 20, 3300), (32, 2, 130, 1040)])
+@pytest.mark.parametrize("Hq,Hkv,B,S", [(8, 8, 34, 2521), (16, 8, 2, 41017), (32, 4, 20, 8257), (32, 2, 130, 2609)])
 def test_cache_policy_changes_no_bits(dev, Hq, Hkv, B, S):
-    """From 128 MiB of keys and values on they are loaded non-temporally; the
-    batch as one such call equals its halves, dense and paged, bit for bit."""
-    assert 2 * B * Hkv * S * 256 >= 128 << 20 > 2 * (B // 2) * Hkv * S * 256
+    """Keys and values of more than 320 MiB are loaded non-temporally; the batch
+    as one such call equals its halves, dense and paged, bit for bit."""
+    assert 2 * B * Hkv * S * 256 > 320 << 20 > 2 * (B // 2) * Hkv * S * 256
     g = torch.Generator(device=dev).manual_seed(S)
     q = torch.randn(B, Hq, 128, device=dev, generator=g).bfloat16()
     k, v = (torch.randn(B, Hkv, S, 128, device=dev, generator=g).bfloat16() for _ in range(2))

@@ -1,0 +1,35 @@
+"""The rules for non-temporal loads (CPU: the host functions themselves)."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2609_24270_amd", "csrc")
+MIB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    """rule(expression) -> the value of a C++ expression over read_policy.h."""
+    def run(*exprs):
+        d = tmp_path_factory.mktemp("policy")
+        src = d / "p.cpp"
+        src.write_text('#include <cstdio>\n#include "read_policy.h"\nusing namespace asym;\nint main() {\n' +
+                       "".join(f'std::printf("%lld\\n", (long long)({e}));\n' for e in exprs) + "}\n")
+        r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(d / "p")],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return [int(x) for x in subprocess.run([str(d / "p")], capture_output=True, text=True).stdout.split()]
+    return run
+
+
+def test_attention_reads_what_the_caches_keep_with_ordinary_loads(rule):
+    # B=1 x 32768 and B=4 x 8192 tokens of 8 heads are 128 MiB, the sizes of placed pages
+    sizes = [33 * MIB, 128 * MIB, 256 * MIB, 320 * MIB, 375 * MIB, 500 * MIB, 8192 * MIB]
+    assert rule(*(f"attn_streams_kv({s}ll)" for s in sizes)) == [0, 0, 0, 0, 1, 1, 1]
+
+
+def test_the_launch_asks_the_rules():
+    capi = open(os.path.join(CSRC, "capi.cpp")).read()
+    assert "a.once = attn_streams_kv(" in capi
