@@ -1125,12 +1125,14 @@ int attn_decode(const asym_topology* topo_in, int B, int Hq, int Hkv, int S, int
   a.split = P.split; a.n_splits = P.n_splits;
   a.n_x = n_x; a.grid = P.grid;
   a.scale = scale;
-  a.once = attn_streams_kv(2ll * B * Hkv * S * D * 2);
+  int64_t kv_bytes = 2ll * B * Hkv * S * D * 2;
   if (paged) {
     a.k_page = k_pages;
     a.v_page = v_pages;
     a.pool_bytes = (uint32_t)(pool_pages * (size_t)attn_page_tokens() * 128 * 2);
+    kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v);
   }
+  a.once = attn_streams_kv(kv_bytes);
   return launch_attn_decode(a, stream);
 }
 

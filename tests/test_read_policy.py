@@ -30,6 +30,15 @@ def test_attention_reads_what_the_caches_keep_with_ordinary_loads(rule):
     assert rule(*(f"attn_streams_kv({s}ll)" for s in sizes)) == [0, 0, 0, 0, 1, 1, 1]
 
 
+def test_pages_that_requests_share_count_once(rule):
+    # 64 requests x 8 heads x 4096 tokens over the pages of one of them: 16 MiB
+    assert rule(f"paged_kv_bytes({1024 * MIB}ll, {8 * MIB}ll, false)", f"paged_kv_bytes({1024 * MIB}ll, {8 * MIB}ll, true)",
+                f"paged_kv_bytes({1024 * MIB}ll, {2048 * MIB}ll, true)", f"paged_kv_bytes({100 * MIB}ll, {400 * MIB}ll, false)",
+                f"attn_streams_kv(paged_kv_bytes({1024 * MIB}ll, {8 * MIB}ll, false))") == [
+                    16 * MIB, 8 * MIB, 1024 * MIB, 100 * MIB, 0]
+
+
 def test_the_launch_asks_the_rules():
     capi = open(os.path.join(CSRC, "capi.cpp")).read()
-    assert "a.once = attn_streams_kv(" in capi
+    assert "a.once = attn_streams_kv(kv_bytes)" in capi
+    assert "kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v)" in capi
