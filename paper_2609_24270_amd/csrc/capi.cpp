@@ -505,14 +505,6 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
   return ASYM_OK;
 }
 
-// Whether data read once per launch is loaded non-temporally: from a quarter of
-// the memory-side cache (256 MiB) on.  Measured, weights cold / resident, us:
-// 32 x 6144 x 4096 (50 MB) 17.6 / 16.9 non-temporal, 16.8 / 14.7 otherwise;
-// 32 x 14336 x 4096 (117 MB) 23.6 / 22.3 and 26.5 / 20.6; 32 groups of 20 rows,
-// 4096 x 2048 (537 MB) 91.1 and 98.1.  A program's other weights and caches
-// pass through that cache between two launches, so the cold figures count.
-static bool streams_past_cache(int64_t bytes) { return bytes >= (64ll << 20); }
-
 // The small-M launch a plan asks for (everything but the partials buffer of
 // a split K, which the caller provides).
 static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void* B, void* C, int M, int N, int K,
@@ -522,11 +514,12 @@ static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void*
   sm.M = M; sm.N = N; sm.K = K; sm.lda = lda; sm.ldb = ldb; sm.ldc = ldc;
   sm.mb = P.small_mb;
   sm.row_tiles = (M + 16 * P.small_mb - 1) / (16 * P.small_mb);
-  sm.b_once = sm.row_tiles == 1 && streams_past_cache((int64_t)N * K * 2);
   sm.order = small_m_order(mapping);
   sm.n_x = P.t->n_xccs;
   sm.device_cus = P.t->n_cus;
   sm.ksplit = small_m_ksplit(M, N, K, P.small_mb, P.t->n_cus);
+  const int range_steps = sm.ksplit > 1 ? ((K + 31) / 32 + sm.ksplit - 1) / sm.ksplit : 0;
+  sm.b_once = sm.row_tiles == 1 && small_m_streams_b(B, ldb, (int64_t)N * K * 2, range_steps);
   sm.tile_cols = small_m_cols(N, P.small_mb, sm.row_tiles, sm.ksplit, P.t->n_cus);
   const int tiles_n = (N + sm.tile_cols - 1) / sm.tile_cols;
   sm.grid = small_m_grid(sm.row_tiles, tiles_n, sm.order, sm.n_x);
@@ -916,7 +909,7 @@ int gemm_grouped_bf16(const asym_topology* topo_in, int G, const int* Ms, int N,
     sm.mb = small_mb;
     sm.n_x = P.t->n_xccs;
     sm.device_cus = P.t->n_cus;
-    sm.b_once = max_rows <= 16 * small_mb && streams_past_cache((int64_t)G * N * K * 2);
+    sm.b_once = max_rows <= 16 * small_mb && small_m_streams_b(B, ldb, (int64_t)G * N * K * 2, 0);
     sm.grid = T;
     sm.d_desc = tb.desc;
     sm.tile_cols = small_w;

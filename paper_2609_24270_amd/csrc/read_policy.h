@@ -33,4 +33,29 @@ inline int64_t paged_kv_bytes(int64_t read, int64_t pool_bytes, bool one_pool) {
   return read < pools ? read : pools;
 }
 
+// B of a small-M product whose rows one workgroup each reads: `bytes` of it, at
+// b with a pitch of ldb bf16 values, in k ranges of `range_steps` 32-wide steps
+// (0: K is not split).  Only where every stage of 64 k is a whole 128-byte line of
+// each row: of a line that two stages share, the second half is gone from the
+// caches when the next stage asks for it.  And only from 64 MiB on.  Measured, us,
+// ordinary loads first, weights just read (resident) and several weights in turn
+// (cold); a program's other weights pass through the memory-side cache between two
+// launches, so the cold figures decide:
+//                                        resident     cold
+//   32 x 6144 x 4096        48 MiB       14.0  16.5   16.5  17.0
+//   32 x 14336 x 4096      112 MiB       19.4  21.9   25.8  23.6
+//   64 x 14336 x 4096      112 MiB       20.4  27.7   29.2  28.0
+//   32 x 20480 x 4096      160 MiB       26.4  30.2   34.6  31.8
+//   8 groups of 20 rows, 4096 x 2048
+//                          128 MiB       21.0  25.6   29.6  27.2
+//   32 groups of them      512 MiB       99.5  91.4   99.7  91.2
+//   rows of 4088 values, half lines: 32 x 20000 x 4088
+//                          156 MiB       26.3  45.3   44.6  47.4
+//   32 groups of 20 rows, 1000 x 2040
+//                          125 MiB       23.2  34.6   31.5  34.1
+inline bool small_m_streams_b(const void* b, int64_t ldb, int64_t bytes, int64_t range_steps) {
+  const bool lines = (reinterpret_cast<uintptr_t>(b) & 127u) == 0 && ldb % 64 == 0 && range_steps % 2 == 0;
+  return lines && bytes >= (64ll << 20);
+}
+
 }  // namespace asym

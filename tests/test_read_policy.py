@@ -38,7 +38,17 @@ def test_pages_that_requests_share_count_once(rule):
                     16 * MIB, 8 * MIB, 1024 * MIB, 100 * MIB, 0]
 
 
+def test_weights_stream_by_whole_lines_only(rule):
+    def b(at, ldb, mib, steps=0):
+        return f"small_m_streams_b((const void*){at}, {ldb}, {mib * MIB}ll, {steps})"
+    assert rule(b(4096, 4096, 64), b(4096, 4096, 63), b(4096, 2048, 512)) == [1, 0, 1]
+    # a pitch of half lines, a first row inside a line, k ranges that start inside one
+    assert rule(b(4096, 2040, 125), b(4096, 4088, 512), b(4096 + 16, 4096, 112), b(4096 + 64, 4096, 112),
+                b(4096, 4096, 112, 16), b(4096, 4096, 112, 15)) == [0, 0, 0, 0, 1, 0]
+
+
 def test_the_launch_asks_the_rules():
     capi = open(os.path.join(CSRC, "capi.cpp")).read()
     assert "a.once = attn_streams_kv(kv_bytes)" in capi
     assert "kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v)" in capi
+    assert capi.count("small_m_streams_b(B, ldb, ") == 2 and capi.count("b_once = ") == 2
