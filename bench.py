@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path: persistent XCD-aware bf16 GEMM on one MI355X.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--studies ...]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--studies ...] [--studies-out FILE]
 
 Workload: square bf16 GEMM M = N = K = 8192, inputs uniform[-1,1] from seed 1,
 B stored [N][K], fp32 accumulation, bf16 output, on the whole GPU; the
@@ -10,8 +10,9 @@ persistent GEMM with the XCD-aware mapping (the schedule is cached after the
 first launch).  W warm-up launches and a few seconds of untimed launches
 (the clock and power state settle) precede the K timed steps.
 
-Studies added to the same line (all on synthetic inputs): the three mappings
-timed interleaved at 8192^3; the decoder-layer shapes; prefill || decode on
+Studies, printed as a second JSON record on stderr or written to --studies-out
+(all on synthetic inputs): the three mappings timed interleaved at 8192^3; the
+decoder-layer shapes; prefill || decode on
 XCD-aligned and CU-striped partitions; the GEMM 4096^3 on 32 random and 2
 XCD-aligned 128-CU sets beside a second tenant, with the max/min spread.
 
@@ -1325,6 +1326,19 @@ def focus_run(name: str, dev, stream, launches: int, mapping: str = "aware") -> 
             "algorithmic_bytes": int(nbytes), "TBps": round(nbytes / (ms * 1e-3) / 1e12, 3)}
 
 
+# The result line's keys: a reader that keeps the last few thousand characters of the output still has the whole
+# line (with the studies in it, it was past 20000).
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+             "vs_baseline", "dtype", "data", "config", "pct_peak", "clock_power", "device", "roofline",
+             "aware_speedup_vs_oblivious_grouped", "aware_speedup_vs_oblivious_rowmajor", "cpu_baseline",
+             "parity_vs_oracle")
+
+
+def split_line(line: dict):
+    """(result line, studies): `line` in two records, the second with every key outside LINE_KEYS."""
+    return ({k: line[k] for k in LINE_KEYS if k in line}, {k: v for k, v in line.items() if k not in LINE_KEYS})
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -1350,6 +1364,8 @@ def main() -> int:
                          "attention decode), parity (every "
                          "configuration's product against the oracle, all outputs); 'none' for "
                          "the headline only")
+    ap.add_argument("--studies-out", default=None,
+                    help="write the studies' JSON record to this file (without it: one line on stderr)")
     ap.add_argument("--spread-masks", type=int, default=32)
     ap.add_argument("--spread-tenants", default="copy",
                     help="comma list of tenants for the CU-set spread study: copy (the 64 MiB "
@@ -1507,7 +1523,16 @@ def main() -> int:
         line["parity_vs_oracle"] = parity
         if args.probe != "identity" and "parity" in studies:
             line["config_parity"] = config_parity(topo, dev, stream)
-    print(json.dumps(line), flush=True)
+    short, rest = split_line(line)
+    if rest:
+        # before the line itself, so that the line stays the last thing printed
+        text = json.dumps(rest)
+        if args.studies_out:
+            with open(args.studies_out, "w") as f:
+                f.write(text + "\n")
+        else:
+            print(text, file=sys.stderr, flush=True)
+    print(json.dumps(short), flush=True)
     return 0
 
 

@@ -49,3 +49,14 @@ def test_no_gpu_output_times_only():
     A, B = _inputs()
     cpu, par = bench.cpu_baseline(A, B, 16)
     assert par is None and cpu["unit"] == "TFLOP/s"
+
+
+def test_result_line_holds_no_studies():
+    """The line keeps the contract's keys, the studies' record everything else, and neither loses any."""
+    contract = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config")
+    full = dict.fromkeys(contract, 1.0)
+    full.update(roofline={"frac": 0.6}, cpu_baseline=None, cu_set_spread={"a": 1}, mla_decode={"b": 2}, topology={})
+    line, studies = bench.split_line(full)
+    assert {**line, **studies} == full and not set(line) & set(studies)
+    assert set(contract) < set(line) and {"cu_set_spread", "mla_decode", "topology"} == set(studies)
