@@ -33,6 +33,21 @@ inline int64_t paged_kv_bytes(int64_t read, int64_t pool_bytes, bool one_pool) {
   return read < pools ? read : pools;
 }
 
+// Paged K and V past that line are loaded with ordinary loads all the same where
+// `tasks` (one a wave) are a second round of 1/8 to 5/8 of the `round` waves that
+// run at a time, and one or two query heads read a key/value head: a wave of that
+// thin round waits longer for each load that passes by the caches, and more heads,
+// or more waves, cover it.  Measured, us, ordinary loads first, 1 / 2 / 4 query
+// heads, 64 key/value heads in all: 1.06 rounds 128.9 129.1 / 131.4 129.9 / 138.8
+// 131.6, 1.25 144.3 145.7 / 146.8 146.8 / 151.5 148.9, 1.375 151.6 155.0 / 154.1
+// 156.2 / 159.3 159.1, 1.56 157.0 158.9 / 159.4 159.7 / 164.4 162.4, 1.66 161.9
+// 160.6 / 164.2 161.9 / 168.1 164.4, 1.78 172.0 163.7; 1.25 rounds of full splits,
+// one query head, 147 and 151 to 153 (dense 143 and 141: the rule is for pages).
+inline bool pages_thin_round(int heads_per_kv, int64_t tasks, int64_t round) {
+  const int64_t last = tasks - round;
+  return heads_per_kv <= 2 && 8 * last > round && 8 * last <= 5 * round;
+}
+
 // B of a small-M product whose rows one workgroup each reads: `bytes` of it, at
 // b with a pitch of ldb bf16 values, in k ranges of `range_steps` 32-wide steps
 // (0: K is not split).  Only where every stage of 64 k is a whole 128-byte line of

@@ -38,6 +38,14 @@ def test_pages_that_requests_share_count_once(rule):
                     16 * MIB, 8 * MIB, 1024 * MIB, 100 * MIB, 0]
 
 
+def test_pages_of_a_thin_second_round_are_not_streamed(rule):
+    def thin(g, tasks, round=2048):
+        return f"pages_thin_round({g}, {tasks}, {round})"
+    # one round, a second one of 1/8 and less, of 1/4, of 5/8 and past it, two rounds, more of them
+    assert rule(*(thin(1, t) for t in (2048, 2304, 2305, 2560, 3328, 3329, 4096, 4608))) == [0, 0, 1, 1, 1, 0, 0, 0]
+    assert rule(thin(2, 2560), thin(4, 2560), thin(1, 1280, 1024), thin(1, 100)) == [1, 0, 1, 0]
+
+
 def test_weights_stream_by_whole_lines_only(rule):
     def b(at, ldb, mib, steps=0):
         return f"small_m_streams_b((const void*){at}, {ldb}, {mib * MIB}ll, {steps})"
@@ -50,5 +58,6 @@ def test_weights_stream_by_whole_lines_only(rule):
 def test_the_launch_asks_the_rules():
     capi = open(os.path.join(CSRC, "capi.cpp")).read()
     assert "a.once = attn_streams_kv(kv_bytes)" in capi
+    assert "if (paged && pages_thin_round(Hq / Hkv, P.tasks, " in capi
     assert "kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v)" in capi
     assert capi.count("small_m_streams_b(B, ldb, ") == 2 and capi.count("b_once = ") == 2
