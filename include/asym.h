@@ -633,12 +633,13 @@ int asym_gemm_noalloc_limits(size_t* scratch_bytes, int* max_tiles, size_t* max_
  * comparable across XCDs. */
 typedef struct asym_wg_record {
   uint64_t start;       /* the workgroup began */
-  uint64_t first_tile;  /* its first tile began (0: it computed none) */
+  uint64_t first_tile;  /* its first tile, or part of one, began (0: it computed none) */
   uint64_t end;         /* it left */
   uint32_t xcc;         /* XCC_ID it ran on */
   uint32_t hw_id;       /* HW_ID register (SE, shader array, CU, SIMD, wave slot) */
-  uint32_t tiles;       /* tiles it computed */
-  uint32_t worked;      /* 1 if it computed a tile */
+  uint32_t tiles;       /* tiles it computed; of tiles computed in parts (asym_gemm_plan), those
+                           whose first part it took: over a launch's records the grid's tiles */
+  uint32_t worked;      /* 1 if it computed a tile or a part of one */
   uint64_t cycles;      /* shader-clock cycles (s_memtime) from start to end: with
                            end - start, the mean clock of the CU it ran on */
 } asym_wg_record;

@@ -1086,7 +1086,7 @@ gemm_bf16_persistent(Params p) {
     }
     tile = read_box(box);
   }
-  if constexpr (TRACE) trace_record(p, t_start, c_start, t_first, n_tiles_done, n_tiles_done > 0);
+  if constexpr (TRACE) trace_record(p, t_start, c_start, n_tiles_done ? t_first : 0ull, n_tiles_done, n_tiles_done > 0);
   if (dyn && threadIdx.x == 0) {
     // the last workgroup to leave resets the counters for the next launch
     __threadfence();
@@ -1133,7 +1133,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
   bool active = true;
   int claimed = 0;
-  const unsigned long long t_first = TRACE ? wall_clock() : 0ull;
+  unsigned long long t_first = 0ull;
   int tiles_done = 0, parts_done = 0;
   for (;;) {
     int item;
@@ -1171,12 +1171,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     tg.n0 += pc * 32 * FN;
     // a part past the product's (or the group's) last row or column is empty
     if (tg.rows > 0 && tg.n0 < p.N) {
-      if constexpr (TRACE) ++parts_done;
+      if constexpr (TRACE) {
+        if (parts_done++ == 0) t_first = wall_clock();  // (behind the rank ticket and the claim)
+      }
       compute_part<FM, FN, NS, DMA>(p, tg, lds);
     }
     if constexpr (TRACE) tiles_done += part == 0;
   }
-  if constexpr (TRACE) trace_record(p, t_start, c_start, parts_done ? t_first : 0ull, tiles_done, parts_done > 0);
+  if constexpr (TRACE) trace_record(p, t_start, c_start, t_first, tiles_done, parts_done > 0);
   if (dyn && threadIdx.x == 0) {
     // the last workgroup to leave resets the counters for the next launch
     __threadfence();

@@ -186,3 +186,35 @@ def test_aligned_operands_into_unaligned_c(M, N, K):
     torch.cuda.synchronize()
     assert np.array_equal(bits(C[:, 1:N + 1]), Co)
     assert torch.all(C[:, 0].cpu() == 3.0) and torch.all(C[:, N + 1].cpu() == 3.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(300, 520, 264), (512, 6144, 512), (1024, 6144, 512), (300, 521, 263)])
+def test_part_trace_records(M, N, K):
+    """Records of a product computed in parts: each tile counted once, `worked` and `first_tile` together, and the
+    claiming form's first part begins behind its rank ticket and claim: two atomics' round trips (1.6 us; the
+    workgroup's setup is the same in both forms).  1024 x 6144 on four XCDs is whole tiles, some workers without one."""
+    dev = torch.device("cuda:0")
+    topo = asym.probe_topology(0, asym.PROBE_IDENTITY)
+    A, B = (x.to(dev) for x in workloads.make_inputs(workloads.make_problem(M, N, K, seed=41)))
+    prev = asym.set_small_m(False)
+    try:
+        ref = asym.gemm(A, B, topo=topo)
+    finally:
+        asym.set_small_m(prev)
+    khz = asym.device_query(0)["wall_clock_khz"]
+    leads = []
+    for xcd_mask in (0, 0x0F):
+        C = torch.zeros_like(ref)
+        t = asym.gemm_trace(A, B, C, topo=topo, xcd_mask=xcd_mask, launches=2)[1]  # (the second: the kernel is loaded)
+        assert torch.equal(C, ref)
+        assert t["plan"]["claims"] == (xcd_mask != 0) and len(t["tiles"]) == t["plan"]["grid"]
+        assert int(t["tiles"].sum()) == t["plan"]["tiles_m"] * t["plan"]["tiles_n"]
+        worked = t["worked"] == 1
+        assert np.array_equal(worked, t["first_tile"] != 0) and worked.any()
+        assert (t["tiles"][~worked] == 0).all()
+        first = t["first_tile"][worked]
+        assert (first >= t["start"][worked]).all() and (first <= t["end"][worked]).all()
+        leads.append(np.median((first - t["start"][worked]).astype(np.float64)) / khz * 1e3)
+    print(f"{M}x{N}x{K}: first part {leads[0]:.2f} us after the start, claimed {leads[1]:.2f}")
+    assert leads[1] >= leads[0] + 0.5
