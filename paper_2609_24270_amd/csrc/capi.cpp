@@ -516,7 +516,7 @@ static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void*
   sm.row_tiles = (M + 16 * P.small_mb - 1) / (16 * P.small_mb);
   sm.order = small_m_order(mapping);
   sm.n_x = P.t->n_xccs;
-  sm.device_cus = P.t->n_cus;
+  sm.set_cus = P.total;
   sm.ksplit = small_m_ksplit(M, N, K, P.small_mb, P.t->n_cus);
   const int range_steps = sm.ksplit > 1 ? ((K + 31) / 32 + sm.ksplit - 1) / sm.ksplit : 0;
   sm.b_once = sm.row_tiles == 1 && small_m_streams_b(B, ldb, (int64_t)N * K * 2, range_steps);
@@ -908,7 +908,7 @@ int gemm_grouped_bf16(const asym_topology* topo_in, int G, const int* Ms, int N,
     sm.M = (int)rows; sm.N = N; sm.K = K; sm.lda = lda; sm.ldb = ldb; sm.ldc = ldc;
     sm.mb = small_mb;
     sm.n_x = P.t->n_xccs;
-    sm.device_cus = P.t->n_cus;
+    sm.set_cus = P.total;
     sm.b_once = max_rows <= 16 * small_mb && small_m_streams_b(B, ldb, (int64_t)G * N * K * 2, 0);
     sm.grid = T;
     sm.d_desc = tb.desc;

@@ -389,11 +389,15 @@ int launch_gemm_small_m(const SmallMLaunch& g, hipStream_t s) {
     return fail(ASYM_EINVAL, "small-M GEMM: a split K needs one row tile and a workspace");
   const long long grid = g.grid;
   if (grid < 1 || grid > (1ll << 31) - 1) return fail(ASYM_EINVAL, "small-M GEMM: grid out of range");
-  // One workgroup per CU at most: the ring takes most of a CU's LDS (72 to 104
-  // KiB of B in flight).  More workgroups than CUs: half of that each, so that
-  // two share a CU and one's start overlaps the other's stream (32 groups of
-  // 20 rows, 4096 x 2048: 98 us against 114 with the deep ring for all).
-  const bool deep = grid <= g.device_cus;
+  // One workgroup per CU of the stream's set at most: the ring takes most of a
+  // CU's LDS (64 to 104 KiB of B in flight).  More workgroups than CUs: half of
+  // that each, so that two share a CU and one's start overlaps the other's stream
+  // (32 groups of 20 rows, 4096 x 2048: 98 us against 114 with the deep ring for
+  // all).  Counted over the whole chip, a product of up to 256 workgroups ran two
+  // rounds of deep rings on a masked stream, each CU idle at every start: 128 CUs,
+  // 128 x 4096 x 4096 28.0 us, now 19.9; 32 x 14336 x 1024 8.6, now 7.0; 32 x
+  // 14336 x 4096 31.7, now 30.5; 64 CUs, 32 x 10240 x 4096 47.9, now 45.2.
+  const bool deep = grid <= g.set_cus;
 #define ASYM_SMALL_M(mb, ns, once)                                                                          \
   hipLaunchKernelGGL((gemm_bf16_small_m<mb, ns, once>), dim3((unsigned)grid), dim3(SK_THREADS), 0, s, p)
 #define ASYM_SMALL_M_CASE(mb, ns_deep, ns)                                       \

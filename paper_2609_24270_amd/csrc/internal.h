@@ -116,7 +116,7 @@ struct SmallMLaunch {
   int row_tiles = 1;            // plain GEMM: row tiles of 16 mb rows
   int order = 0;                // plain GEMM: 0 aware, 1 column-major, 2 row-major
   int n_x = 8;                  // XCDs
-  int device_cus = 256;         // compute units of the device
+  int set_cus = 256;            // compute units that run the launch's workgroups (the stream's set)
   bool b_once = false;          // B is loaded non-temporally: one workgroup per row of it, and more than a cache keeps
   long long grid = 0;           // workgroups
   const void* d_desc = nullptr; // grouped: device int4 per workgroup {row, rows, B row, column}

@@ -146,6 +146,27 @@ def test_cu_masked_stream_bitwise(dev):
         asym.stream_destroy(s)
 
 
+@pytest.mark.parametrize("M", [16, 32, 64])
+@pytest.mark.parametrize("N,K", [(1024, 2056), (14336, 1024), (16384, 328)])
+def test_ring_depth_on_a_masked_stream(dev, M, N, K):
+    """Workgroups up to the set's CUs, and past them but not past the device's."""
+    topo = asym.probe_topology(0, asym.PROBE_IDENTITY | asym.PROBE_MASKMAP)
+    A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M, dist="int"))
+    Ad, Bd = A.to(dev), B.to(dev)
+    cols = np.unique(np.concatenate([np.random.default_rng(N).choice(N, 200, replace=False), np.arange(N - 80, N)]))
+    _, Co = oracle.gemm_bf16(bits(A), bits(B)[cols], "nk")
+    s = asym.stream_create(topo, workloads.random_mask_bits(11, 1, 128)[0])
+    try:
+        plan = asym.gemm_plan(A=Ad, B=Bd, topo=topo, stream=s)
+        assert plan["small_m"] == 1 and (plan["grid"] <= 128 if N == 1024 else 128 < plan["grid"] <= 256), plan
+        torch.cuda.synchronize()
+        C = asym.gemm(Ad, Bd, topo=topo, stream=s)
+        s.synchronize()
+        assert np.array_equal(bits(C)[:, cols], Co)
+    finally:
+        asym.stream_destroy(s)
+
+
 def test_grouped_small_groups_exact_integer_equals_persistent(dev):
     p = workloads.grouped_problem(32, 20, 4096, 2048, seed=5, dist="int")
     Ms, A, B = workloads.make_grouped_inputs(p)

@@ -1,10 +1,11 @@
 """What a short call pays for: work that only longer calls need must stand
 behind a branch (CPU: the compiled kernels; GPU: results at those sizes)."""
+import os
 import re
 
 import pytest
 
-from tests.test_kernel_fragments import blocks_of
+from tests.test_kernel_fragments import CSRC, blocks_of
 from tests.test_kernel_structure import asm_of
 
 
@@ -39,3 +40,10 @@ def test_small_m_ring_loads_only_the_stages_there_are(tmp_path):
         assert sum(n > 2 * lps for n in loads) == 1, (k, loads)
         assert any(n == lps and not m for n, m in zip(loads, mfmas)), (k, loads)
         assert loads[mfmas.index(max(mfmas))] == 0, (k, loads, mfmas)
+
+
+def test_the_ring_depth_counts_the_streams_cus():
+    """The deep ring takes a whole CU: it is for launches of one workgroup per CU of the set they run on."""
+    capi, skinny = (open(os.path.join(CSRC, f)).read() for f in ("capi.cpp", "gemm_skinny.hip"))
+    assert capi.count("  SmallMLaunch sm;\n") == 2 == capi.count("sm.set_cus = P.total;")
+    assert "const bool deep = grid <= g.set_cus;" in skinny
