@@ -508,7 +508,7 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
 // The small-M launch a plan asks for (everything but the partials buffer of
 // a split K, which the caller provides).
 static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void* B, void* C, int M, int N, int K,
-                                   int lda, int ldb, int ldc, int mapping) {
+                                   int lda, int ldb, int ldc, int mapping, bool b_fresh = false) {
   SmallMLaunch sm;
   sm.A = A; sm.B = B; sm.C = C;
   sm.M = M; sm.N = N; sm.K = K; sm.lda = lda; sm.ldb = ldb; sm.ldc = ldc;
@@ -519,7 +519,7 @@ static SmallMLaunch small_m_launch(const GemmPlan& P, const void* A, const void*
   sm.set_cus = P.total;
   sm.ksplit = small_m_ksplit(M, N, K, P.small_mb, P.t->n_cus);
   const int range_steps = sm.ksplit > 1 ? ((K + 31) / 32 + sm.ksplit - 1) / sm.ksplit : 0;
-  sm.b_once = sm.row_tiles == 1 && small_m_streams_b(B, ldb, (int64_t)N * K * 2, range_steps);
+  sm.b_once = sm.row_tiles == 1 && small_m_streams_b(B, ldb, (int64_t)N * K * 2, range_steps, b_fresh);
   sm.tile_cols = small_m_cols(N, P.small_mb, sm.row_tiles, sm.ksplit, P.t->n_cus);
   const int tiles_n = (N + sm.tile_cols - 1) / sm.tile_cols;
   sm.grid = small_m_grid(sm.row_tiles, tiles_n, sm.order, sm.n_x);
@@ -535,7 +535,7 @@ static size_t small_m_part_bytes(const SmallMLaunch& sm) {
 
 static int gemm_bf16_locked(const asym_topology* topo_in, int M, int N, int K, const void* A, int lda,
                             const void* B, int ldb, int b_layout, void* C, int ldc, int mapping,
-                            uint32_t xcd_mask, hipStream_t stream);
+                            uint32_t xcd_mask, hipStream_t stream, bool b_fresh = false);
 
 int gemm_bf16(const asym_topology* topo_in, int M, int N, int K, const void* A, int lda,
               const void* B, int ldb, int b_layout, void* C, int ldc, int mapping,
@@ -565,17 +565,17 @@ int gemm_bf16(const asym_topology* topo_in, int M, int N, int K, const void* A, 
   rc = launch_transpose_bf16(B, K, N, ldb, ws->kn_buf, ldt, stream);
   if (rc != ASYM_OK) return rc;
   return gemm_bf16_locked(topo_in, M, N, K, A, lda, ws->kn_buf, ldt, ASYM_B_NK, C, ldc, mapping, xcd_mask,
-                          stream);
+                          stream, true);
 }
 
 static int gemm_bf16_locked(const asym_topology* topo_in, int M, int N, int K, const void* A, int lda,
                             const void* B, int ldb, int b_layout, void* C, int ldc, int mapping,
-                            uint32_t xcd_mask, hipStream_t stream) {
+                            uint32_t xcd_mask, hipStream_t stream, bool b_fresh) {
   GemmPlan P;
   int rc = plan_gemm(topo_in, M, N, K, A, lda, B, ldb, b_layout, C, ldc, mapping, xcd_mask, stream, &P);
   if (rc != ASYM_OK) return rc;
   if (P.small_mb) {
-    SmallMLaunch sm = small_m_launch(P, A, B, C, M, N, K, lda, ldb, ldc, mapping);
+    SmallMLaunch sm = small_m_launch(P, A, B, C, M, N, K, lda, ldb, ldc, mapping, b_fresh);
     if (sm.ksplit > 1) {
       Workspace* ws = nullptr;
       rc = get_workspace(P.device, stream, &ws);

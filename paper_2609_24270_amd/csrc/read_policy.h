@@ -68,9 +68,17 @@ inline bool pages_thin_round(int heads_per_kv, int64_t tasks, int64_t round) {
 //                          156 MiB       26.3  45.3   44.6  47.4
 //   32 groups of 20 rows, 1000 x 2040
 //                          125 MiB       23.2  34.6   31.5  34.1
-inline bool small_m_streams_b(const void* b, int64_t ldb, int64_t bytes, int64_t range_steps) {
+// A copy that the launch before has just written (`fresh`: the transpose of B
+// stored [K][N]) is still in the memory-side cache while it and its source fit
+// there.  Whole calls, us, ordinary loads first, several weights in turn:
+//   32 x 4096 x 14336       112 MiB       61.0  70.9   (64 rows 63.1  77.0)
+//   32 x 14336 x 4096       112 MiB       58.3  61.8   (64 rows 59.9  65.2)
+//   16 x 8192 x 8192        128 MiB       74.7  74.3   (resident 74.5  70.4)
+//   16 x 20480 x 4096       160 MiB       90.1  90.9
+//   32 x 30000 x 4096       234 MiB      167.8 150.1
+inline bool small_m_streams_b(const void* b, int64_t ldb, int64_t bytes, int64_t range_steps, bool fresh = false) {
   const bool lines = (reinterpret_cast<uintptr_t>(b) & 127u) == 0 && ldb % 64 == 0 && range_steps % 2 == 0;
-  return lines && bytes >= (64ll << 20);
+  return lines && bytes >= ((fresh ? 128ll : 64ll) << 20);
 }
 
 }  // namespace asym

@@ -55,9 +55,18 @@ def test_weights_stream_by_whole_lines_only(rule):
                 b(4096, 4096, 112, 16), b(4096, 4096, 112, 15)) == [0, 0, 0, 0, 1, 0]
 
 
+def test_a_fresh_copy_is_read_from_the_caches(rule):
+    def b(mib, fresh):
+        return f"small_m_streams_b((const void*)4096, 4096, {mib * MIB}ll, 0, {fresh})"
+    assert rule(b(112, 0), b(112, 1), b(127, 1), b(128, 1)) == [1, 0, 0, 1]
+
+
 def test_the_launch_asks_the_rules():
     capi = open(os.path.join(CSRC, "capi.cpp")).read()
     assert "a.once = attn_streams_kv(kv_bytes)" in capi
     assert "if (paged && pages_thin_round(Hq / Hkv, P.tasks, " in capi
     assert "kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v)" in capi
     assert capi.count("small_m_streams_b(B, ldb, ") == 2 and capi.count("b_once = ") == 2
+    # the [K][N] path says that its B is a copy of this call
+    assert capi.count("ws->kn_buf, ldt, ASYM_B_NK, C, ldc, mapping, xcd_mask,\n                          stream, true)") == 1
+    assert "range_steps, b_fresh)" in capi and "lda, ldb, ldc, mapping, b_fresh)" in capi
