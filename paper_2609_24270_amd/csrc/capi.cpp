@@ -1125,7 +1125,7 @@ int attn_decode(const asym_topology* topo_in, int B, int Hq, int Hkv, int S, int
     a.pool_bytes = (uint32_t)(pool_pages * (size_t)attn_page_tokens() * 128 * 2);
     kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v);
   }
-  a.once = attn_streams_kv(kv_bytes);
+  a.once = attn_streams_kv(kv_bytes) && attn_set_streams(P.cs.total, P.cs.t->n_cus);
   // (two claiming workgroups a CU)
   if (paged && pages_thin_round(Hq / Hkv, P.tasks, 2ll * P.cs.total * attn_tasks_per_workgroup())) a.once = false;
   return launch_attn_decode(a, stream);

@@ -33,6 +33,14 @@ inline int64_t paged_kv_bytes(int64_t read, int64_t pool_bytes, bool one_pool) {
   return read < pools ? read : pools;
 }
 
+// Only where nearly the whole chip reads them: on fewer CUs the waves in flight,
+// not HBM, bound the call, and each wave waits longer for a load that passes by
+// the caches.  Measured, us, ordinary loads first, 16 requests x 8000 tokens of 8
+// heads / 64 x 8000 of 8 / 16 x 4000 of 32: 64 CUs 218 243 / 806 930 / 365 454,
+// 128 CUs 121 135 / 444 511 / 213 251, 192 CUs 129 135 / 382 402 / 231 251, 224
+// CUs 136 132 / 408 404 / 242 253, 240 CUs 134 126 / 412 406 / 239 233.
+inline bool attn_set_streams(int set_cus, int device_cus) { return 16 * set_cus >= 15 * device_cus; }
+
 // Paged K and V past that line are loaded with ordinary loads all the same where
 // `tasks` (one a wave) are a second round of 1/8 to 5/8 of the `round` waves that
 // run at a time, and one or two query heads read a key/value head: a wave of that

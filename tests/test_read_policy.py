@@ -30,6 +30,10 @@ def test_attention_reads_what_the_caches_keep_with_ordinary_loads(rule):
     assert rule(*(f"attn_streams_kv({s}ll)" for s in sizes)) == [0, 0, 0, 0, 1, 1, 1]
 
 
+def test_small_cu_sets_read_with_ordinary_loads(rule):
+    assert rule(*(f"attn_set_streams({n}, 256)" for n in (64, 128, 224, 239, 240, 256))) == [0, 0, 0, 0, 1, 1]
+
+
 def test_pages_that_requests_share_count_once(rule):
     # 64 requests x 8 heads x 4096 tokens over the pages of one of them: 16 MiB
     assert rule(f"paged_kv_bytes({1024 * MIB}ll, {8 * MIB}ll, false)", f"paged_kv_bytes({1024 * MIB}ll, {8 * MIB}ll, true)",
@@ -63,7 +67,7 @@ def test_a_fresh_copy_is_read_from_the_caches(rule):
 
 def test_the_launch_asks_the_rules():
     capi = open(os.path.join(CSRC, "capi.cpp")).read()
-    assert "a.once = attn_streams_kv(kv_bytes)" in capi
+    assert "a.once = attn_streams_kv(kv_bytes) && attn_set_streams(P.cs.total, P.cs.t->n_cus);" in capi
     assert "if (paged && pages_thin_round(Hq / Hkv, P.tasks, " in capi
     assert "kv_bytes = paged_kv_bytes(kv_bytes, a.pool_bytes, k == v)" in capi
     assert capi.count("small_m_streams_b(B, ldb, ") == 2 and capi.count("b_once = ") == 2
