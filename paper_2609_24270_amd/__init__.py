@@ -668,10 +668,12 @@ def stream_destroy(stream) -> None:
 def _stream_ptr(stream):
     """The hipStream_t of a torch stream, or of torch's current one, as an int.
     (torch.cuda.current_stream() builds a Stream object for it, 2.6 us of a
-    call's 9.5 us of host time; the handle alone takes 0.2.)"""
+    call's 9.5 us of host time; the handle alone takes 0.2.  A torch without
+    that name takes the object's.)"""
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 

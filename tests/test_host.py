@@ -517,3 +517,17 @@ def test_mla_form_level_switch(lib):
         assert asym.set_mla_workgroup_form(2) == 3
     finally:
         asym.set_mla_workgroup_form(prev)
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """The current stream's handle comes from torch's raw getter, or from its stream object where there is none."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x5A0))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0x1000 + d, raising=False)
+    assert asym._stream_ptr(None) == 0x1003
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert asym._stream_ptr(None) == 0x5A0
+    assert asym._stream_ptr(types.SimpleNamespace(cuda_stream=7)) == 7
