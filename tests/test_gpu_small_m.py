@@ -317,9 +317,9 @@ def test_narrow_column_tiles(dev, M, N, K, width):
     assert_gemm_close(outs[0][:, cols], R, what=f"{M}x{N}x{K} in {width}-column tiles")
 
 
-# both ring depths (workgroups up to, and past, the 256 CUs), B on both sides of
-# the size from which rows read once bypass the caches (64 MiB), K shorter than
-# the ring, odd and even stage counts and a last stage of one 8-k chunk
+# K shorter than the ring, odd and even stage counts and a last stage of one 8-k
+# chunk, in both ring depths (130 rows of these run on the persistent kernel's
+# tiles or parts)
 @pytest.mark.parametrize("M", [3, 32, 50, 130])
 @pytest.mark.parametrize("N,K", [(16392, 2056), (16384, 2040), (40000, 8), (17000, 328), (16000, 904)])
 def test_ring_depths_and_cache_policy(dev, M, N, K):
@@ -333,6 +333,39 @@ def test_ring_depths_and_cache_policy(dev, M, N, K):
         asym.gemm(Ad, Bd, C[:, :N], mapping=m)
         assert torch.all(C[:, N:] == 3.0)
         assert np.array_equal(bits(C[:, :N])[:, cols], Co), m
+
+
+# every kernel there is, by ring depth (workgroups up to the device's CUs, or more) and by whether B is loaded
+# non-temporally (one row tile, whole lines, 64 MiB and more)
+@pytest.mark.parametrize("M", [16, 32, 64])
+@pytest.mark.parametrize("N,K,deep,once", [(14336, 4096, True, True), (32768, 1024, False, True),
+                                           (14336, 1024, True, False), (20000, 1024, False, False)])
+def test_each_depth_with_each_cache_policy(dev, M, N, K, deep, once):
+    A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M + K, dist="int"))
+    Ad, Bd = A.to(dev), B.to(dev)
+    C = torch.full((M, N + 4), 3.0, dtype=torch.bfloat16, device=dev)
+    plan = asym.gemm_plan(Ad, Bd, C[:, :N])
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    assert plan["small_m"] == 1 and plan["k_splits"] == 1 and plan["tiles_m"] == 1, plan
+    assert (plan["grid"] <= cus) == deep and (N * K * 2 >= 64 << 20 and K % 64 == 0) == once
+    cols = np.unique(np.concatenate([np.random.default_rng(N).choice(N, 300, replace=False), np.arange(N - 80, N)]))
+    _, Co = oracle.gemm_bf16(bits(A), bits(B)[cols], "nk")
+    asym.gemm(Ad, Bd, C[:, :N])
+    assert torch.all(C[:, N:] == 3.0) and np.array_equal(bits(C[:, :N])[:, cols], Co)
+
+
+# B that two and three row tiles read
+@pytest.mark.parametrize("M", [100, 130])
+@pytest.mark.parametrize("N,K", [(8192, 4104), (4096, 8192)])
+def test_several_row_tiles(dev, M, N, K):
+    A, B = workloads.make_inputs(workloads.make_problem(M, N, K, seed=M + K, dist="int"))
+    Ad, Bd = A.to(dev), B.to(dev)
+    plan = asym.gemm_plan(Ad, Bd, torch.empty(M, N, dtype=torch.bfloat16, device=dev))
+    assert plan["small_m"] == 1 and plan["tiles_m"] == (M + 63) // 64, plan
+    cols = np.unique(np.concatenate([np.random.default_rng(N).choice(N, 300, replace=False), np.arange(N - 80, N)]))
+    _, Co = oracle.gemm_bf16(bits(A), bits(B)[cols], "nk")
+    for m in MAPS:
+        assert np.array_equal(bits(asym.gemm(Ad, Bd, mapping=m))[:, cols], Co), m
 
 
 @pytest.mark.parametrize("M", [3, 20, 50])  # 16, 32 and 64 rows a tile: rings of 14 and 7, 12 and 6, 9 and 5 slots
