@@ -240,8 +240,8 @@ struct GemmPlan {
 // Products whose tiles do not fill the workers compute each tile in parts, one
 // workgroup each (the deep-ring kernel): the smallest part with which one round
 // of workgroups still covers the product, since a part's time per k-stage grows
-// with its size (64 x 64: 0.21 us, 128 x 64: 0.30, 128 x 96: 0.41, 128 x 128:
-// 0.46, 128 x 192: 0.60, on a full chip) and a second round costs a whole part.
+// with its size (64 x 64: 0.20 us, 128 x 64: 0.33, 128 x 96: 0.39, 128 x 128:
+// 0.46, 128 x 192: 0.62, on a full chip) and a second round costs a whole part.
 // Measured (K = 4096, us): 512 x 6144 in 128 x 96 parts 29.4, 128 x 128 31.7,
 // 64 x 64 (three rounds) 44.0; 1024 x 4096 in 128 x 128 33.3, 128 x 64 (two
 // rounds) 43.5.  256-row tiles that fill at most half the workers are cut in
@@ -253,7 +253,7 @@ struct GemmPlan {
 // not take (`ring` false: A, B or C off their alignment) always run in parts:
 // with A and B loaded through registers 128 x 128 ones at most (a wider one's
 // registers do not fit): 1000 x 3001 x 1501 24.2 us, in the element-wise loads
-// it replaced 92.1; 4001 x 4001 x 4095 196 against 1009.
+// it replaced 92.1; 4001 x 4001 x 4095 188 to 200, by box, against 1009.
 static void choose_parts(int M, int N, bool ring, GemmPlan* P) {
   auto tiles = [&](int64_t h, int64_t w) { return ((M + h - 1) / h) * ((N + w - 1) / w); };
   if (P->bm == 128) {
@@ -284,15 +284,15 @@ std::atomic<int> g_mla_form{2};
 
 // Up to 64 rows (per group) the small-M kernel streams B at HBM rate, where
 // 256-row tiles compute padding (32 groups of 20 rows, 4096 x 2048: 90 us
-// against 140) and output parts fetch few stages ahead (32 x 4096 x 14336: 24.3
-// against 41.2; 32 x 14336 x 4096 with its weights resident is a draw, 22.1 and
-// 21.3).  From 65 to kSmallMMaxRows rows it runs 64-row tiles, and each of them
+// against 140) and output parts fetch few stages ahead (32 x 4096 x 14336: 23.7
+// against 41.3; 32 x 14336 x 4096 with its weights resident is a draw, 21.1 and
+// 21.4).  From 65 to kSmallMMaxRows rows it runs 64-row tiles, and each of them
 // re-reads the shared A fragments from LDS in every wave: it was drawn against
 // the 256-row tiles, which it beats while its workgroups fit about two per CU
 // (128 x 4096 x 4096 29.7 against 53.8 us).  Output parts, which plain products
-// of these sizes would run on otherwise, are faster for some (15.1 against 18.1
-// there, 128 x 14336 x 4096 24.1 against 28.7); the plan of such sizes is
-// asserted and reported to callers, so the line stays.
+// of these sizes would run on otherwise, are a draw there (15.4 against 15.8) and
+// faster with more columns (128 x 14336 x 4096 24.6 against 28.2); the line is
+// still the one drawn against whole tiles.
 constexpr int kSmallMMaxRows = 256;
 
 int small_m_for(const GemmPlan& P, int max_rows, long long wgs_at_64_rows) {
@@ -312,7 +312,7 @@ int small_m_order(int mapping) {
   return mapping == ASYM_MAP_AWARE ? 0 : mapping == ASYM_MAP_OBLIVIOUS_GROUPED ? 1 : 2;
 }
 
-// A CU reads HBM at about 20-24 GB/s at most, so a single row tile with fewer
+// A CU reads HBM at 20 to 26 GB/s at most, so a single row tile with fewer
 // 64-column tiles than the device has CUs splits K into ranges, one workgroup
 // each (up to 8, each range at least two stages of k-steps); a second launch
 // adds the ranges' fp32 tiles in range order (the launch boundary makes the
@@ -331,10 +331,12 @@ int small_m_ksplit(int M, int N, int K, int mb, int device_cus) {
   const int u = mb == 4 ? 4 : 8;
   // only when the column tiles leave half the CUs idle, then about two
   // workgroups per CU in a power of two of ranges, each of 8 (4) k-steps or
-  // more.  Measured, weights cold, us: 16 x 2048 x 8192 (32 column tiles) 23.2
-  // unsplit, 18.6 in 2 ranges, 12.9 in 8; 32 x 4096 x 4096 (64) 14.6, 14.2 and
-  // 12.7; 32 x 6144 x 4096 (96) 15.1, 16.4 and 16.7, but resident 14.4, 13.1
-  // and 14.7.
+  // more.  Measured, unsplit, in 2 and in 8 ranges, us, weights cold / resident:
+  // 16 x 2048 x 8192 (32 column tiles) 20.9, 17.7 and 11.6 / 19.8, 13.3 and 8.6;
+  // 32 x 4096 x 4096 (64) 12.6, 13.2 and 12.3 / 11.8, 10.1 and 10.5; 32 x 6144 x
+  // 4096 (96) 13.1, 15.3 and 15.5 / 12.3, 11.8 and 13.7.  Up there the split
+  // gains nothing any more (it did before B came through the ring, 18.6 and 15.4
+  // in 2 and 8 ranges), but it orders the sums, and so fixes the result's bits.
   if (2 * tiles > device_cus) return 1;
   int ks = 1;
   while (ks < 8 && (long long)ks * tiles < 2ll * device_cus) ks *= 2;
@@ -344,11 +346,11 @@ int small_m_ksplit(int M, int N, int K, int mb, int device_cus) {
 
 // An unsplit product takes the column-tile width, a multiple of 8 up to 64,
 // that minimises what the busiest CU reads: ceil(workgroups / CUs) x (the
-// tile's 16 mb rows of A + its columns of B, per k), since a CU reads at about
-// 20-24 GB/s at most.  A narrower width is taken only when that saves at least
+// tile's 16 mb rows of A + its columns of B, per k), since the CU that reads most
+// ends last (a CU streams 20 to 26 GB/s).  A narrower width is taken only when that saves at least
 // 7% over 64 columns (the widest on ties; measured, weights cold, us, 64
-// columns first: 32 x 14336 x 4096 in 56 columns, 24.2 and 23.5; 32 x 10240 x
-// 4096 in 40, 20.7 and 18.0; 128 x 4096 x 4096 in 32, 21.7 and 18.3).
+// columns first: 32 x 14336 x 4096 in 56 columns, 22.8 and 21.6; 32 x 10240 x
+// 4096 in 40, 19.4 and 16.2; 128 x 4096 x 4096 in 32, 20.5 and 17.2).
 // A wave with no columns at a tile's edge computes nothing; a narrower wave is
 // the same case as the product's edge, and each output is still one wave's
 // MFMA chain over all of K: the bits do not change.
@@ -474,9 +476,9 @@ static int plan_gemm(const asym_topology* topo_in, int M, int N, int K, const vo
   P->bm = (int)BMr;
   P->bn = ring ? choose_tile_width(M, N, total) : (int)BNr;
   // A product whose 256 x 256 tiles would leave three quarters of the workers
-  // idle takes 128 x 128 tiles on the register-staged path: four times the
-  // tiles, at most one round (512^3: 16 tiles instead of 4).  Each output is
-  // the same MFMA chain either way, so the bits do not change.
+  // idle takes 128 x 128 tiles: four times the tiles, at most one round (512^3:
+  // 16 tiles instead of 4), each computed in parts (below).  Each output is the
+  // same MFMA chain either way, so the bits do not change.
   if (small_tiles && ((int64_t)(M + BMr - 1) / BMr) * ((N + BNr - 1) / BNr) * 4 <= total) {
     P->bm = 128;
     P->bn = 128;
@@ -1204,8 +1206,8 @@ static int mla_plan(const asym_topology* topo_in, int B, int Hq, int S, int spli
   // 64-head form staged its rows in registers (B=8, S=16384: 62.4 us halved
   // against 73.0); with both forms as they are the 64-head form's 1024-token
   // splits, which write half the partials, would lead (59.1 against 53.5;
-  // B=16, S=8192: 60.1 and 53.8).  The plan is asserted for such a size and
-  // reported to callers, so it stays.
+  // B=16, S=8192: 60.1 and 53.8).  The split count orders the merge's sums: at
+  // another line these sizes would give other bits.
   if (!split_in && allow == 2 && fits128 && L >= 1024 && 2 * t128 <= set_cus && 4 * t128 > set_cus) {
     L /= 2;
     n_splits = (S + L - 1) / L;

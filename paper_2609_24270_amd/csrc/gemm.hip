@@ -604,10 +604,11 @@ __device__ __forceinline__ void compute_tile_ring(const Params& pin, int tile, u
 // What bounds it: the loads into LDS.  A 128 x 128 part takes 32 KiB of them per
 // 64-wide k-stage; alone, with the MFMAs and the LDS reads left out, they take
 // 0.34 us a stage with all CUs busy (97 GB/s per CU), the MFMAs alone 0.30, the
-// LDS reads alone 0.13, all together 0.43.  A wider part needs fewer bytes per
+// LDS reads alone 0.13, all together 0.43 (in the whole kernel 0.46, over K from
+// 4096 to 12288).  A wider part needs fewer bytes per
 // output, so parts are as large as one round of workgroups allows.  The loads
 // of a stage take about a microsecond to arrive: the ring holds NS stages (4 of
-// 32 to 40 KiB, 6 of the smaller ones; more measured the same or slower, as the
+// 28 to 40 KiB, 6 of the smaller ones; more measured the same or slower, as the
 // first stage then waits behind more loads), where the register-staged
 // tiles that served these products before had one stage in flight and waited a
 // memory round trip per stage (512 x 6144 x 4096: 55.1 us, now 28.9; 1024 x
@@ -758,8 +759,8 @@ __device__ __forceinline__ void compute_part(const Params& p, const TileGeom& tg
     // values instead, which are shifted down to its place, zeros behind them,
     // when the chunk is written; a K of fewer than kFirst whole stages (it may
     // be below 8) is loaded value by value.  Bound by the loads' round trips and
-    // their second lines (a chunk row spans two): 0.73 us a stage at 128 x 128
-    // against 0.43 direct; with two-byte loads one stage ahead it took 3.8.
+    // their second lines (a chunk row spans two): 0.69 us a stage at 128 x 128
+    // against 0.46 direct; with two-byte loads one stage ahead it took 3.8.
     uint32_t off[LPS];
 #pragma unroll
     for (int j = 0; j < LPS; ++j)

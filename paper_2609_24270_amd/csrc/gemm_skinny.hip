@@ -10,14 +10,14 @@
 // in stages of 64 k, eight lanes per whole 128-byte line of a row, with NS - 1
 // stages in flight and one barrier per stage; the fragments of a stage are read
 // while the one before it is computed.  What bounds it is the rate one CU
-// streams at (20-24 GB/s from HBM) and how soon it gets there.  Before, a wave
+// streams at (20 to 26 GB/s from HBM) and how soon it gets there.  Before, a wave
 // loaded its B fragments straight into operand registers, 64 bytes of 16 rows
 // per load, half lines that the vector cache takes twice: 32 x 14336 x 4096
-// (weights not in any cache) 32.2 us, now 23.4 (5.0 TB/s); 64 rows 46.7, now
-// 26.6; 32 groups of 20 rows, 6144 x 7168, 495, now 419 (6.7 TB/s).  A tenth of
+// (weights not in any cache) 32.2 us, now 22.0 (5.3 TB/s); 64 rows 46.7, now
+// 26.2; 32 groups of 20 rows, 6144 x 7168, 495, now 418 (6.8 TB/s).  A tenth of
 // it is the cache policy: B rows that one workgroup reads alone are loaded
-// non-temporally (26.0 against 23.4 us; 464 against 419), rows that several row
-// tiles share are not (128 x 14336 x 4096 40.6 us, non-temporal 42.1).
+// non-temporally (464 against 418), rows that several row tiles share are not
+// (128 x 14336 x 4096 40.6 us, non-temporal 42.1).
 // Each output element is one wave's MFMA chain over k in order, as in the
 // persistent kernel.  Every B byte is fetched once and no tile is reused, so
 // there is no placement to choose: the grid is a plain launch over the tiles.

@@ -100,7 +100,7 @@ struct GemmLaunch {
   int tiles_m, tiles_n;
   int n_xccs;
   bool vec;                    // aligned vector path
-  int bn;                      // tile width: 256, or 224 / 192 on the vector path; 128 with bm = 128
+  int bn;                      // tile width: 256, or 224 / 192 on the vector path; 128 or 96 with bm = 128
   int bm = 256;                // tile height: 256 or 128
   int pm = 0, pn = 0;          // > 0: each tile is computed in parts of pm x pn, one workgroup each
   const void* d_desc = nullptr; // grouped GEMM: device int4 per tile {row, rows, group B row, column}
