@@ -672,8 +672,10 @@ def _stream_ptr(stream):
     that name takes the object's.)"""
     if stream is None:
         import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 
