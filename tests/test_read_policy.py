@@ -26,7 +26,7 @@ def rule(tmp_path_factory):
 
 def test_attention_reads_what_the_caches_keep_with_ordinary_loads(rule):
     # B=1 x 32768 and B=4 x 8192 tokens of 8 heads are 128 MiB, the sizes of placed pages
-    sizes = [33 * MIB, 128 * MIB, 256 * MIB, 320 * MIB, 375 * MIB, 500 * MIB, 8192 * MIB]
+    sizes = [33 * MIB, 128 * MIB, 200 * MIB, 256 * MIB - 1, 256 * MIB, 500 * MIB, 8192 * MIB]
     assert rule(*(f"attn_streams_kv({s}ll)" for s in sizes)) == [0, 0, 0, 0, 1, 1, 1]
 
 
